@@ -60,11 +60,14 @@ DESCRIPTIONS = {
 
 
 def kernel_source_hash() -> str:
-    """sha256 of the source of the streaming kernel (bgk_device.h holds
-    k_stream and everything it inlines): traffic counters are reported only
-    while the kernel is the one they were taken from."""
-    with open(os.path.join(ROOT, "paper_0903_4044_amd", "csrc", "bgk_device.h"), "rb") as fh:
-        return hashlib.sha256(fh.read()).hexdigest()
+    """sha256 of the sources of the streaming kernels (bgk_device.h holds
+    k_stream and everything it inlines, bgk_tile.h k_tile): traffic counters
+    are reported only while the kernel is the one they were taken from."""
+    h = hashlib.sha256()
+    for name in ("bgk_device.h", "bgk_tile.h"):
+        with open(os.path.join(ROOT, "paper_0903_4044_amd", "csrc", name), "rb") as fh:
+            h.update(fh.read())
+    return h.hexdigest()
 
 
 def read_traffic(workload: str, kname: str = "k_stream"):

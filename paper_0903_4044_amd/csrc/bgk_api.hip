@@ -2,6 +2,7 @@
 // The C ABI is declared in include/bgk.h.
 #include "bgk_adjoint.h"
 #include "bgk_device.h"
+#include "bgk_tile.h"
 
 #include <hip/hip_runtime.h>
 
@@ -43,6 +44,10 @@ struct bgk_ctx {
     int sblock = 256;          // streaming kernel: threads per workgroup
     int unroll = 1;            // streaming kernel: jz values whose loads are issued together
     int persist = 0;           // streaming kernel: 0 one workgroup per item, else resident workgroups per CU
+    // tile streaming (k_tile, the shape's vec = 1 where it fits): tiles over all
+    // instances, chunks of p-groups per tile
+    bool tile_ok = false;
+    int ntt = 0, tsplit = 1;
     bool shift = false;        // every instance streams in the translation form (k_shift)
     // translation form in row tiles (k_shift_rows, the shape's unroll = 2):
     // cells per tile, log2 lanes per cell, window cells, tiles, LDS bytes
@@ -127,6 +132,11 @@ static int kind_dim(int k)
     return 1;
 }
 
+// Does the streaming pass run on tiles of cells, and the partial moment sums
+// per cell it leaves.
+static bool use_tile(const bgk_ctx *c) { return c->tile_ok && c->vec == 1; }
+static int num_parts(const bgk_ctx *c) { return use_tile(c) ? c->tsplit : c->vsplit; }
+
 static Args make_args(const bgk_ctx *c)
 {
     Args a;
@@ -138,7 +148,8 @@ static Args make_args(const bgk_ctx *c)
     a.npseudo = c->npseudo;
     a.vsplit = c->vsplit;
     a.zr = c->zr;
-    a.nparts = c->vsplit;
+    a.nparts = num_parts(c);
+    a.nttiles = c->ntt;
     a.ntiles = c->row_ntiles;
     a.pass = c->pass;
     a.rec = nullptr;
@@ -333,6 +344,17 @@ static void task_shape(const Geo &g, int vec, int zchunk, int *zr_out, int *bloc
     }
 }
 
+static int vsplit_for(const bgk_ctx *c, int target_wg)
+{
+    return std::max(1, std::min(c->geo.nvz, (target_wg + c->ncells - 1) / c->ncells));
+}
+
+// jz chunks per cell that give the per-cell kernels enough workgroups.
+static int default_vsplit(const bgk_ctx *c)
+{
+    return vsplit_for(c, c->dim == 1 ? (c->precision == BGK_FP32 ? 1024 : 512) : 2048);
+}
+
 static void set_shape(bgk_ctx *c, int vec, int unroll, int vsplit, int persist = 0)
 {
     drop_graphs(c);
@@ -342,12 +364,13 @@ static void set_shape(bgk_ctx *c, int vec, int unroll, int vsplit, int persist =
     c->persist = persist;
     c->vsplit = std::max(1, std::min(c->vsplit_max, vsplit));
     if (c->shift && unroll == 2) c->vsplit = g.nvz;  // row tiles: one plane per work item
+    if (use_tile(c)) {
+        // the shape's chunks are the tiles' p-group chunks; the per-cell kernels
+        // (moments, closing relaxation, reverse sweep) keep jz chunks of their own
+        c->tsplit = c->vsplit;
+        c->vsplit = std::min(c->vsplit_max, default_vsplit(c));
+    }
     task_shape(g, c->vec, g.nvz / c->vsplit, &c->zr, &c->sblock);
-}
-
-static int vsplit_for(const bgk_ctx *c, int target_wg)
-{
-    return std::max(1, std::min(c->geo.nvz, (target_wg + c->ncells - 1) / c->ncells));
 }
 
 // Translation form in row tiles: lanes per cell G = 2^lg >= N_vx (at most
@@ -399,13 +422,79 @@ static void plan_rows(bgk_ctx *c)
     c->row_lds_bytes = lds;
 }
 
+// Tile streaming (k_tile): cells per tile, p-groups (64 consecutive (jx, jy))
+// per cell and the workgroups the device holds at once.
+struct TilePlan { int tx, ty, npg, slots; size_t lds; };
+
+template <typename real, int DIM>
+static TilePlan tile_plan(const bgk_ctx *c)
+{
+    using S = TileShape<real, DIM>;
+    const size_t lds = tile_lds<real, DIM>(c->geo).total + sizeof(TileRow) * S::NROW + 36 * S::NW * sizeof(double);
+    const int per_cu = std::max(1, std::min((sizeof(real) == 4 ? 16 : 8) / S::NW, (int)((size_t)c->lds_max / lds)));
+    return {S::TX, S::TY, (c->geo.npl + 63) / 64, per_cu * c->ncu, lds};
+}
+
+static TilePlan tile_plan(const bgk_ctx *c)
+{
+    if (c->precision == BGK_FP64) return c->dim == 1 ? tile_plan<double, 1>(c) : tile_plan<double, 2>(c);
+    return c->dim == 1 ? tile_plan<float, 1>(c) : tile_plan<float, 2>(c);
+}
+
+static void plan_tile(bgk_ctx *c)
+{
+    c->tile_ok = false;
+    if (c->dim == 3 || c->shift || c->geo.npl < 64) return;
+    const TilePlan P = tile_plan(c);
+    if (P.lds > (size_t)c->lds_max) return;
+    long long tiles = 0;
+    for (Inst &I : c->h_inst) {
+        I.ttile0 = (int)tiles;
+        tiles += (long long)((I.nx + P.tx - 1) / P.tx) * ((I.ny + P.ty - 1) / P.ty);
+    }
+    // Where the per-cell kernel stays: too few (tile, p-group) units to fill the
+    // device (a unit of 24 planes takes ~40 us whatever the grid), or tiles
+    // largely outside the domain.  Steps measured as per-cell / tile, us:
+    // FP32 2D 33x29 x 24^3 (180 units, 256 slots) 79 / 72, 24x24 (81) 63 / 75,
+    // 17x150 (padded 1.43 times) 159 / 173; FP64 2D 33x29 x 16^3 (160 of 256)
+    // 75 / 53, 16x16 (32) 52 / 52; FP32 1D 256 x 48^3 (576 of 1024) 93 / 87,
+    // 2000 x 16^3 (500) 31 / 33; FP64 1D 2000 x 32^3 (2000 of 512) 278 / 234,
+    // 700 (704) 107 / 107, 256 (256) 36 / 45.
+    const bool d = c->precision == BGK_FP64;
+    const double fill = c->dim == 2 ? (d ? 0.25 : 0.7) : (d ? 2.0 : 0.55), pad = d ? 1.7 : 1.35;
+    if ((double)tiles * P.npg < fill * P.slots || (double)tiles * P.tx * P.ty > pad * c->ncells) return;
+    c->tile_ok = true;
+    c->ntt = (int)tiles;
+}
+
+// p-groups are shared out over v chunks per tile: the v of the least
+// makespan, rounds of workgroups times p-groups per chunk (0.2: what a
+// workgroup spends on its tables), whole rounds counted while there are few.
+static int tile_chunks(const bgk_ctx *c, int vmax)
+{
+    const TilePlan P = tile_plan(c);
+    int best = 1;
+    double cost = 1e300;
+    for (int v = 1; v <= std::min(P.npg, vmax); ++v) {
+        const double x = (double)c->ntt * v / P.slots;
+        const double k = x <= 4.0 ? std::ceil(x) * ((P.npg + v - 1) / v + 0.2) : (x + 0.5) * ((double)P.npg / v + 0.2);
+        if (k < cost * (1.0 - 1e-9)) {
+            cost = k;
+            best = v;
+        }
+    }
+    return best;
+}
+
 // Default shape (measured on MI355X for the paper's grids; bgk_autotune refines it).
-static void choose_launch(bgk_ctx *c)
+static void choose_launch(bgk_ctx *c, bool keep_scratch)
 {
     // up to 4 jz chunks per cell even on large grids: smaller work items keep
     // the y-neighbour rows of the cells in flight resident in each XCD's L2
     c->vsplit_max = std::max(vsplit_for(c, 8192), std::min(c->geo.nvz, 4));
     if (c->row_ok) c->vsplit_max = std::max(c->vsplit_max, c->geo.nvz);
+    // (keep_scratch: no more partial sums than the per-cell kernel takes)
+    const int tile_vmax = keep_scratch ? c->vsplit_max : NVMAX * NVMAX / 64;
     int vec = 1;
     for (int v : {4, 2})
         if (vec_valid(c, v)) { vec = v; break; }
@@ -413,14 +502,21 @@ static void choose_launch(bgk_ctx *c)
     int unroll = (c->dim == 1 && c->precision == BGK_FP32 && !c->shift) ? 2 : 1;
     // translation form: row tiles when their plane-by-tile items fill the device
     if (c->shift && c->row_ok && c->row_ntiles * c->geo.nvz >= c->ncu) unroll = 2;
-    const int target = c->dim == 1 ? (c->precision == BGK_FP32 ? 1024 : 512) : 2048;
-    set_shape(c, vec, unroll, vsplit_for(c, target));
+    int vsplit = default_vsplit(c);
+    if (c->tile_ok) {
+        const int v = tile_chunks(c, tile_vmax);
+        c->vsplit_max = std::max(c->vsplit_max, v);
+        vec = 1;
+        vsplit = v;
+    }
+    set_shape(c, vec, unroll, vsplit);
 }
 
 // Host-side set-up of a context: validation, geometry, instance tables,
 // time steps and the default launch shape.  No device memory is touched.
 // Returns a status code and sets msg on failure.
-static int plan_ctx(const bgk_problem *probs, int n_probs, int precision, bgk_ctx *c, std::string &msg)
+static int plan_ctx(const bgk_problem *probs, int n_probs, int precision, bgk_ctx *c, std::string &msg,
+                    bool keep_scratch = false)
 {
     if (!probs || n_probs < 1) {
         msg = "need at least one problem";
@@ -578,8 +674,9 @@ static int plan_ctx(const bgk_problem *probs, int n_probs, int precision, bgk_ct
     for (int i = 0; i < n_probs; ++i) c->h_inst[i].pseudo0 = c->ncells + c->h_pseudo_prefix[i];
     c->f_elems = (size_t)f_off;
     if (c->shift) plan_rows(c);
+    plan_tile(c);
 
-    choose_launch(c);
+    choose_launch(c, keep_scratch);
     return BGK_OK;
 }
 
@@ -713,6 +810,7 @@ static Args pointwise_args(const bgk_ctx *c)
 {
     Args a = make_args(c);
     if (c->shift && c->unroll == 2) a.vsplit = std::min(c->vsplit, vsplit_for(c, 2048));
+    a.vsplit = std::min(a.vsplit, a.nparts);
     return a;
 }
 
@@ -852,6 +950,19 @@ static void stream_dispatch(bgk_ctx *c, int nb, size_t lds, const void *src, voi
     }
 }
 
+template <typename real, int DIM, bool REC>
+static void launch_tile(bgk_ctx *c, Args a, const void *src, void *dst, const real *p, hipStream_t s)
+{
+    a.vsplit = a.nparts;
+    const size_t lds = tile_lds<real, DIM>(c->geo).total;
+    auto go = [&](auto kern) {
+        hipLaunchKernelGGL(kern, dim3(c->ntt * a.vsplit), dim3(64 * TileShape<real, DIM>::NW), lds, s, a,
+                           (const real *)src, (real *)dst, p, c->partial);
+    };
+    if (stream_nt(c)) go(k_tile<real, DIM, true, REC>);
+    else go(k_tile<real, DIM, false, REC>);
+}
+
 template <typename real>
 static int launch_stream(bgk_ctx *c, const void *src, void *dst, hipStream_t s)
 {
@@ -905,6 +1016,10 @@ static int launch_stream(bgk_ctx *c, const void *src, void *dst, hipStream_t s)
         else
             hipLaunchKernelGGL((k_shift<real, false, false>), dim3(nb), dim3(c->sblock), 0, s, a, (const real *)src,
                                (real *)dst, p, c->partial);
+    } else if (use_tile(c)) {
+        const real *p = (const real *)params_buf<real>(c, c->pass_parity);
+        if (c->dim == 1) launch_tile<real, 1, false>(c, make_args(c), src, dst, p, s);
+        else launch_tile<real, 2, false>(c, make_args(c), src, dst, p, s);
     } else if (c->dim == 3) stream_dispatch<real, 3>(c, nb, lds, src, dst, s);
     else if (c->dim == 2) stream_dispatch<real, 2>(c, nb, lds, src, dst, s);
     else stream_dispatch<real, 1>(c, nb, lds, src, dst, s);
@@ -944,7 +1059,7 @@ static int one_pass(bgk_ctx *c, int k, int n, const void *src, void *dst, hipStr
 {
     c->pass_parity = (k - 1) % 2;
     TRY(launch_stream<real>(c, src, dst, s));
-    return launch_prep<real>(c, k < n ? MODE_MID : MODE_FINAL, c->vsplit, k % 2, s);
+    return launch_prep<real>(c, k < n ? MODE_MID : MODE_FINAL, num_parts(c), k % 2, s);
 }
 
 // Every launch of n >= 1 steps after the rounding counter is set: the
@@ -954,7 +1069,7 @@ template <typename real>
 static int step_launches(bgk_ctx *c, const void *f_in, void *f_out, int n, hipStream_t s)
 {
     TRY(launch_moments<real>(c, f_in, s));
-    TRY(launch_prep<real>(c, MODE_FIRST, c->vsplit, 0, s));
+    TRY(launch_prep<real>(c, MODE_FIRST, num_parts(c), 0, s));
     auto X = [&](int k) -> void * { return k == 0 ? const_cast<void *>(f_in) : ((n - k) % 2 == 0 ? f_out : c->work); };
     for (int k = 1; k <= n; ++k) TRY(one_pass<real>(c, k, n, X(k - 1), X(k), s));
     return launch_final<real>(c, f_out, f_out, n % 2, s);
@@ -1116,6 +1231,11 @@ static int launch_stream_rec(bgk_ctx *c, const void *src, void *dst, unsigned ch
 {
     Args a = make_args(c);
     a.rec = rec;
+    if (use_tile(c)) {
+        launch_tile<real, DIM, true>(c, a, src, dst, params_buf<real>(c, 0), s);
+        HIP_TRY(c, hipGetLastError());
+        return BGK_OK;
+    }
     int block = 256;
     task_shape(c->geo, 1, c->geo.nvz / c->vsplit, &a.zr, &block);
     const int nb = c->ncells * c->vsplit;
@@ -1217,7 +1337,7 @@ static int do_adjoint(bgk_ctx *c, const void *f, const void *lam_next, void *lam
     TRY(fill(c, c->gt, c->ncells, 0.0, s));
     TRY(launch_moments<real>(c, f, s));
     TRY(relax_info<real>(c, c->info_f, 0, s));
-    TRY(launch_prep<real>(c, MODE_FIRST, c->vsplit, 0, s));
+    TRY(launch_prep<real>(c, MODE_FIRST, num_parts(c), 0, s));
     c->pass_parity = 0;
     unsigned char *br = (unsigned char *)c->adj_rec;
     if (c->dim == 1) TRY((launch_stream_rec<real, 1>(c, f, c->adj_h, br, s)));
@@ -1255,7 +1375,7 @@ static int part_totals(bgk_ctx *c, double *tot, hipStream_t s)
 
 static int part_restore(bgk_ctx *c, const double *tot, hipStream_t s)
 {
-    const long long n = (long long)c->ncells * c->vsplit * NQ;
+    const long long n = (long long)c->ncells * num_parts(c) * NQ;
     hipLaunchKernelGGL(k_part_restore, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, make_args(c), tot,
                        c->partial);
     HIP_TRY(c, hipGetLastError());
@@ -1273,14 +1393,14 @@ static int do_step_record(bgk_ctx *c, const void *f_in, void *f_out, char *rec, 
     HIP_TRY(c, hipGetLastError());
     c->seed += 1u;
     TRY(launch_moments<real>(c, f_in, s));
-    TRY(launch_prep<real>(c, MODE_FIRST, c->vsplit, 0, s));
+    TRY(launch_prep<real>(c, MODE_FIRST, num_parts(c), 0, s));
     TRY(part_totals(c, (double *)(rec + L.tot_f), s));
     c->pass_parity = 0;
     unsigned char *br = (unsigned char *)(rec + L.br);
     if (c->dim == 1) TRY((launch_stream_rec<real, 1>(c, f_in, rec + L.h, br, s)));
     else TRY((launch_stream_rec<real, 2>(c, f_in, rec + L.h, br, s)));
     TRY(part_totals(c, (double *)(rec + L.tot_h), s));
-    TRY(launch_prep<real>(c, MODE_FINAL, c->vsplit, 1, s));
+    TRY(launch_prep<real>(c, MODE_FINAL, num_parts(c), 1, s));
     return launch_final<real>(c, rec + L.h, f_out, 1, s);
 }
 
@@ -1295,7 +1415,7 @@ static int do_adjoint_record(bgk_ctx *c, const void *f, const char *rec, const v
     TRY(fill(c, c->gt, c->ncells, 0.0, s));
     TRY(part_restore(c, (const double *)(rec + L.tot_f), s));
     TRY(relax_info<real>(c, c->info_f, 0, s));
-    TRY(launch_prep<real>(c, MODE_FIRST, c->vsplit, 0, s));
+    TRY(launch_prep<real>(c, MODE_FIRST, num_parts(c), 0, s));
     TRY(part_restore(c, (const double *)(rec + L.tot_h), s));
     TRY(relax_info<real>(c, c->info_h, 1, s));
     return adjoint_tail<real>(c, f, rec + L.h, (const unsigned char *)(rec + L.br), lam_next, lam_n, grad, s);
@@ -1323,7 +1443,7 @@ static int do_adjoint_sweep(bgk_ctx *c, int n, const void *const *f, const void 
         // step i's opening relaxation data and tables
         TRY(part_restore(c, (const double *)(R(i) + L.tot_f), s));
         TRY(relax_info<real>(c, c->info_f, 0, s));
-        TRY(launch_prep<real>(c, MODE_FIRST, c->vsplit, 0, s));
+        TRY(launch_prep<real>(c, MODE_FIRST, num_parts(c), 0, s));
         if (i == n - 1 || !fuse) {
             // R_b^T coefficients of step i from its own sums at h
             TRY(part_restore(c, (const double *)(R(i) + L.tot_h), s));
@@ -1617,9 +1737,9 @@ template <typename real>
 static int autotune(bgk_ctx *c, const void *f, void *tmp, hipStream_t s)
 {
     TRY(launch_moments<real>(c, f, s));
-    TRY(launch_prep<real>(c, MODE_FIRST, c->vsplit, 0, s));
+    TRY(launch_prep<real>(c, MODE_FIRST, num_parts(c), 0, s));
     struct Cand { double us; int vec, unroll, vsplit, persist; };
-    const Cand start{0.0, c->vec, c->unroll, c->vsplit, c->persist};
+    const Cand start{0.0, c->vec, c->unroll, use_tile(c) ? c->tsplit : c->vsplit, c->persist};
     std::vector<Cand> cands;
     std::vector<int> splits;
     for (int t : {256, 512, 1024, 2048, 4096, 8192}) {
@@ -1638,12 +1758,17 @@ static int autotune(bgk_ctx *c, const void *f, void *tmp, hipStream_t s)
         double us = 0.0;
         for (int r = 0; r < 3 && !rc; ++r) rc = time_steps<real>(c, f, tmp, s, &us);
     }
+    std::vector<int> tsplits;  // chunks of p-groups per tile
+    for (int v : {1, 2, 3, 4, 6, 9, 12, 18, start.vsplit})
+        if (v <= c->vsplit_max && std::find(tsplits.begin(), tsplits.end(), v) == tsplits.end()) tsplits.push_back(v);
     for (int vec : {4, 2, 1}) {
         if (!vec_valid(c, vec)) continue;
+        const bool tile = c->tile_ok && vec == 1;  // one kernel, a plain grid
         for (int unroll : {1, 2, 3, 4})
-            for (int vs : splits)
+            for (int vs : tile ? tsplits : splits)
                 for (int ps : {0, 2, 4}) {
                     if (rc) break;
+                    if (tile && (unroll > 1 || ps)) continue;
                     if (c->shift && unroll > (c->row_ok ? 2 : 1)) continue;  // per-cell or row tiles
                     if (c->dim == 3 && unroll > 2) continue;  // 3D: modes 1 and 2 only
                     if (ps && c->ncells * vs <= ps * c->ncu) continue;  // grid already resident
@@ -1694,7 +1819,7 @@ extern "C" int bgk_get_launch(const bgk_ctx *ctx, int *vec, int *unroll, int *vs
     if (!ctx) return BGK_E_INVALID;
     if (vec) *vec = ctx->vec;
     if (unroll) *unroll = ctx->unroll;
-    if (vsplit) *vsplit = ctx->vsplit;
+    if (vsplit) *vsplit = use_tile(ctx) ? ctx->tsplit : ctx->vsplit;
     if (persist) *persist = ctx->persist;
     if (tuned_us) *tuned_us = ctx->tuned_us;
     return BGK_OK;
@@ -1894,7 +2019,7 @@ extern "C" int bgk_step_noalloc(const bgk_problem *probs, int n_probs, int preci
 {
     bgk_ctx c;  // host-side plan; its device pointers are carved from the scratch array
     std::string msg;
-    int rc = plan_ctx(probs, n_probs, precision, &c, msg);
+    int rc = plan_ctx(probs, n_probs, precision, &c, msg, true);
     if (rc) return fail(nullptr, rc, msg);
     // layout of the scratch array, 256-byte aligned pieces
     auto up = [](size_t x) { return (x + 255) & ~(size_t)255; };

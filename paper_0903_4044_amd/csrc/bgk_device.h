@@ -58,6 +58,7 @@ struct Inst {
     // translation-form streaming in row tiles: first tile of the instance,
     // and the sources' reach below and above a tile (cells, with a margin)
     int tile0, reach_lo, reach_hi;
+    int ttile0;     // tile streaming (k_tile): first tile of the instance
 };
 
 // Streaming directions of an instance.
@@ -88,6 +89,7 @@ struct Args {
     int vsplit;                 // velocity chunks (along jz) per cell
     int zr;                     // jz residues per streaming workgroup (lane tasks)
     int nparts;                 // partial moment sums per cell that consumers add up
+    int nttiles;                // tile streaming (k_tile): tiles over all instances
     int ntiles;                 // row-tile translation streaming: tiles over all instances
     uint32_t *pass;             // rounding counter: advanced once per streaming pass
     unsigned char *rec;         // branch record of a recording streaming pass (else unused)
@@ -141,6 +143,20 @@ __device__ __forceinline__ int strip_cell(const Inst &I, int q)
     const int r = q - nfull * span;
     const int iy = r / rem;
     return iz * pl + iy * I.nx + nfull * W + (r - iy * rem);
+}
+
+// The same for tiles of cells: position q of an instance of tpr tiles per row
+// and tpc rows of tiles, in strips W tiles wide.  Returns row * tpr + column.
+__device__ __forceinline__ int strip_tile(int q, int tpr, int tpc, int W)
+{
+    W = min(W, tpr);
+    const int span = W * tpc, nfull = tpr / W;
+    if (q < nfull * span) {
+        const int k = q / span, r = q - k * span, iy = r / W;
+        return iy * tpr + k * W + (r - iy * W);
+    }
+    const int rem = tpr - nfull * W, r = q - nfull * span, iy = r / rem;
+    return iy * tpr + nfull * W + (r - iy * rem);
 }
 
 // Order of the streaming kernel's (cell, jz chunk) items: superblocks of
