@@ -979,24 +979,26 @@ __device__ __forceinline__ void prep_ghost(const Args &A, int e, int mode, const
 // largest velocity axis, so few lanes idle on small grids; every sum is a
 // butterfly inside the segment, and a segment's results equal those of a
 // whole wave with the extra lanes holding zeros).
-// The table entries of one preparation: cells (GHOST = false, entries
-// [0, ncells)) or ghost sources (GHOST = true, entries [ncells, nentries)),
-// two launches, so that the cells' kernel keeps its state in registers (the
-// ghost faces index per-axis sums with a run-time axis).
-template <typename real, int W, bool GHOST, bool CONS>
+// PART: the entries of one launch -- cells ([0, ncells)), ghost sources
+// ([ncells, nentries)), or both, the ghosts' workgroups first (theirs is the
+// longer chain).
+enum { PREP_CELLS, PREP_GHOSTS, PREP_BOTH };
+template <typename real, int W, int PART, bool CONS>
 __global__ void __launch_bounds__(256) k_prep(Args A, const double *__restrict__ partial, real *__restrict__ params,
                                               int mode, int nentries, real *__restrict__ params_shock_copy)
 {
     // Tables of these modes follow a streaming pass: advance the rounding
     // counter once (stream order puts this after that pass's reads).
-    if (!GHOST && blockIdx.x == 0 && threadIdx.x == 0 && (mode == MODE_MID || mode == MODE_FINAL))
+    if (PART != PREP_GHOSTS && blockIdx.x == 0 && threadIdx.x == 0 && (mode == MODE_MID || mode == MODE_FINAL))
         A.pass[0] = A.pass[0] + 1u;
-    const int e = (GHOST ? A.ncells : 0) + (blockIdx.x * 4 + (threadIdx.x >> 6)) * (64 / W) +
-                  (int)((threadIdx.x & 63) / W);
-    if (e >= (GHOST ? nentries : A.ncells)) return;  // the whole segment leaves; sums never leave a segment
-    if constexpr (!GHOST) {
-        prep_cell<real, W, CONS>(A, e, mode, partial, params);
-    } else {
+    constexpr int PER = 4 * (64 / W);  // entries per workgroup
+    const int gb = PART == PREP_BOTH ? (nentries - A.ncells + PER - 1) / PER : 0;
+    const bool ghost = PART == PREP_GHOSTS || (PART == PREP_BOTH && (int)blockIdx.x < gb);
+    const int e = (ghost ? A.ncells : 0) + ((int)blockIdx.x - (ghost ? 0 : gb)) * PER + (int)threadIdx.x / W;
+    if (e >= (ghost ? nentries : A.ncells)) return;  // the whole segment leaves; sums never leave a segment
+    if (!ghost) {
+        if constexpr (PART != PREP_GHOSTS) prep_cell<real, W, CONS>(A, e, mode, partial, params);
+    } else if constexpr (PART != PREP_CELLS) {
         prep_ghost<real, W, CONS>(A, e, mode, partial, params);
         // Far-field entries never change: give the other parity buffer a copy.
         if (params_shock_copy) {
