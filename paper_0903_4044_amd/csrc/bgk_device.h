@@ -1764,6 +1764,99 @@ __global__ void __launch_bounds__(256)
     }
 }
 
+// The same for planes of at most 64 (jx, jy): W lanes (the smallest of 16, 32,
+// 64 that holds the plane) per (cell, jz chunk), 256 / W of them per
+// workgroup, no LDS and no barrier.  Such a cell is a few elements per lane,
+// and in k_shift the workgroup's set-up (v_z weights, staging, block sum) took
+// all of the time: 18432 cells x 30 x 1 x 2 FP32 43 us a pass, 11 here.  What
+// remains is the chain from the source's table entry to the segment's sum
+// (five butterflies), 9216 waves of it.
+template <typename real, int W, bool NTSTORE>
+__global__ void __launch_bounds__(256)
+    k_shift_cells(Args A, const real *__restrict__ src, real *__restrict__ dst, const real *__restrict__ params,
+                  double *__restrict__ partial)
+{
+    const Geo &g = A.g;
+    const int L = xcd_remap(blockIdx.x, gridDim.x) * (256 / W) + (int)threadIdx.x / W;
+    if (L >= A.ncells * A.vsplit) return;  // the whole segment leaves; sums never leave a segment
+    const int lane = threadIdx.x & (W - 1), gq = L / A.vsplit, split = L - gq * A.vsplit;
+    const Inst &I = A.inst[find_inst(A.cell_prefix, A.ninst, gq)];
+    const int c = gq - I.cell0, p = min(lane, g.npl - 1);
+    int z0, z1;
+    chunk_bounds(g.nvz, A.vsplit, split, &z0, &z1);
+    const int jy = p / g.nvx, jx = p - jy * g.nvx;
+    const double vx = vnode(g, 0, jx), vy = vnode(g, 1, jy);
+    int m, sgn, cell[2], par[2];
+    double ac;
+    shift_of(g, I, jx, &m, &sgn, &ac);
+    const real th = (real)(ac - (double)m);
+    const real *E[2], *h[2];
+    real c0[2], l1[2], l2[2];
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+        shift_source(I, c, sgn, m, k, &cell[k], &par[k]);
+        E[k] = params + (long long)par[k] * g.pe;
+        h[k] = src + I.f0 + (long long)cell[k] * g.nv + p;
+        c0[k] = E[k][0];
+        l1[k] = E[k][g.tx1 + jx] * E[k][g.ty1 + jy];
+        l2[k] = E[k][g.tx2 + jx] * E[k][g.ty2 + jy];
+    }
+    // c0 - 1 of source a as a two-float sum (float path)
+    float c0m1_hi = 0.0f, c0m1_lo = 0.0f;
+    uint32_t key = 0;
+    if constexpr (sizeof(real) == 4) {
+        const double c0m1 = *reinterpret_cast<const double *>(E[0] + 2) - 1.0;
+        c0m1_hi = (float)c0m1;
+        c0m1_lo = (float)(c0m1 - (double)c0m1_hi);
+        key = pass_key(A.pass, 0);
+    }
+    const uint32_t e0 = (uint32_t)c * (uint32_t)g.nv + (uint32_t)p;
+    real *out = dst + I.f0 + e0;
+    double A0 = 0.0, Az = 0.0, Azz = 0.0;
+    // (reduced spaces, the common ones here, hold two planes: unrolled, both
+    // planes' loads are in flight together)
+#pragma unroll 2
+    for (int jz = z0; jz < z1; ++jz) {
+        const uint32_t zo = (uint32_t)jz * (uint32_t)g.npl;
+        const real ha = h[0][zo], hb = h[1][zo];
+        const real a0 = E[0][g.tz + 2 * jz], b0 = E[0][g.tz + 2 * jz + 1];
+        const real a1 = E[1][g.tz + 2 * jz], b1 = E[1][g.tz + 2 * jz + 1];
+        const real M = l1[0] * a0 + l2[0] * b0;
+        const real dx = th * ((c0[0] * ha + M) - (c0[1] * hb + (l1[1] * a1 + l2[1] * b1))), dy = 0;
+        real r;
+        if constexpr (sizeof(real) == 4) {
+            const bool odd = (jz & 1) != 0;
+            // (dx + 0 as in k_shift: the product is rounded, not fused into the difference)
+            const float d = __builtin_fmaf(c0m1_hi, ha, __builtin_fmaf(c0m1_lo, ha, M)) - (dx + dy);
+            const uint32_t hs = hash32((e0 + zo - (odd ? (uint32_t)g.npl : 0u)) ^ key);
+            r = round_stochastic16((double)ha + (double)d, __builtin_amdgcn_ubfe(hs, odd ? 16u : 0u, 16u));
+        } else {
+            r = (c0[0] * ha + M) - dx;
+        }
+        // (lanes beyond the plane repeat the last value)
+        if constexpr (NTSTORE) __builtin_nontemporal_store(r, out + zo);
+        else out[zo] = r;
+        const ZW w = zweights(g, jz);
+        A0 += (double)r;
+        Az += (g.red ? w.m : w.z) * (double)r;
+        Azz += w.zz * (double)r;
+    }
+    double acc[NQ];
+#pragma unroll
+    for (int q = 0; q < NQ; ++q) acc[q] = 0.0;
+    if (lane >= g.npl) A0 = Az = Azz = 0.0;
+    if (g.red) fold_column(acc, vx, vy, Az, 0.0, Azz);
+    else fold_column(acc, vx, vy, A0, Az, Azz);
+    // the five moments (no wall reads half-range fluxes in translation form)
+    double mine = 0.0;
+#pragma unroll
+    for (int q = 0; q < 5; ++q) {
+        const double t = wave_sum<W>(acc[q]);
+        if (lane == q) mine = t;
+    }
+    if (lane < NQ) partial[(long long)L * NQ + lane] = mine;
+}
+
 // ---------------------------------------------------------------- shift, row tiles
 // The translation form again, organised for coalesced access.  At a fixed
 // velocity the sources of consecutive cells are consecutive cells, but the
