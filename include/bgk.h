@@ -226,9 +226,9 @@ int bgk_check(bgk_ctx *ctx, const void *f, void *stream);
  * per stage, 2 or 3 planes ahead), jz chunks per cell (one work item each,
  * 1 .. a context-dependent maximum), and persist: 0 launches one workgroup
  * per work item, k > 0 launches k workgroups per compute unit that walk the
- * items of all instances (one persistent launch for a batch).  Where one-
- * and two-dimensional kinds have enough cells to fill the device with tiles
- * of them, vec 1 is the kernel on tiles: vsplit then counts chunks of (jx,
+ * items of all instances (one persistent launch for a batch).  Where there
+ * are enough cells to fill the device with tiles of them (3D kinds: BGK_FP32
+ * only), vec 1 is the kernel on tiles: vsplit then counts chunks of (jx,
  * jy) groups per tile, unroll and persist have no effect.  Vec is 1
  * for BGK_SHIFT streaming, reduced velocity spaces and 3D kinds; 3D kinds
  * take unroll 1 or 2.  BGK_SHIFT contexts take unroll 1 (the per-cell

@@ -47,7 +47,7 @@ struct bgk_ctx {
     // tile streaming (k_tile, the shape's vec = 1 where it fits): tiles over all
     // instances, chunks of p-groups per tile
     bool tile_ok = false;
-    int ntt = 0, tsplit = 1;
+    int ntt = 0, nti = 0, tsplit = 1;
     bool shift = false;        // every instance streams in the translation form (k_shift)
     // translation form in row tiles (k_shift_rows, the shape's unroll = 2):
     // cells per tile, log2 lanes per cell, window cells, tiles, LDS bytes
@@ -425,7 +425,7 @@ static void plan_rows(bgk_ctx *c)
 
 // Tile streaming (k_tile): cells per tile, p-groups (64 consecutive (jx, jy))
 // per cell and the workgroups the device holds at once.
-struct TilePlan { int tx, ty, npg, slots; size_t lds; };
+struct TilePlan { int tx, ty, tz, npg, slots; size_t lds; };
 
 template <typename real, int DIM>
 static TilePlan tile_plan(const bgk_ctx *c)
@@ -433,11 +433,14 @@ static TilePlan tile_plan(const bgk_ctx *c)
     using S = TileShape<real, DIM>;
     const size_t lds = tile_lds<real, DIM>(c->geo).total + sizeof(TileRow) * S::NROW + 36 * S::NW * sizeof(double);
     const int per_cu = std::max(1, std::min((sizeof(real) == 4 ? 16 : 8) / S::NW, (int)((size_t)c->lds_max / lds)));
-    return {S::TX, S::TY, (c->geo.npl + 63) / 64, per_cu * c->ncu, lds};
+    return {S::TX, S::TY, 1, (c->geo.npl + 63) / 64, per_cu * c->ncu, lds};
 }
 
 static TilePlan tile_plan(const bgk_ctx *c)
 {
+    if (c->dim == 3)  // float only
+        return {4, 4, 4, (c->geo.npl + 63) / 64, c->ncu,
+                tile3_lds(c->geo, true).total + (sizeof(TileRow) + 2 * sizeof(float)) * Tile3::NROW + Tile3::T * Tile3::T * Tile3::T * NQ * sizeof(double)};
     if (c->precision == BGK_FP64) return c->dim == 1 ? tile_plan<double, 1>(c) : tile_plan<double, 2>(c);
     return c->dim == 1 ? tile_plan<float, 1>(c) : tile_plan<float, 2>(c);
 }
@@ -445,13 +448,16 @@ static TilePlan tile_plan(const bgk_ctx *c)
 static void plan_tile(bgk_ctx *c)
 {
     c->tile_ok = false;
-    if (c->dim == 3 || c->shift || c->geo.npl < 64) return;
+    if ((c->dim == 3 && c->precision == BGK_FP64) || c->shift || c->geo.npl < 64) return;
     const TilePlan P = tile_plan(c);
     if (P.lds > (size_t)c->lds_max) return;
     long long tiles = 0;
+    long long inner = 0;  // 3D: tiles whose halo lies inside the instance
     for (Inst &I : c->h_inst) {
-        I.ttile0 = (int)tiles;
-        tiles += (long long)((I.nx + P.tx - 1) / P.tx) * ((I.ny + P.ty - 1) / P.ty);
+        I.ttile0 = (int)(tiles - inner);
+        I.itile0 = (int)inner;
+        if (c->dim == 3) inner += (long long)tile3_inner(I.nx) * tile3_inner(I.ny) * tile3_inner(I.nz);
+        tiles += (long long)((I.nx + P.tx - 1) / P.tx) * ((I.ny + P.ty - 1) / P.ty) * ((I.nz + P.tz - 1) / P.tz);
     }
     // Where the per-cell kernel stays: too few (tile, p-group) units to fill the
     // device (a unit of 24 planes takes ~40 us whatever the grid), or tiles
@@ -460,12 +466,14 @@ static void plan_tile(bgk_ctx *c)
     // 17x150 (padded 1.43 times) 159 / 173; FP64 2D 33x29 x 16^3 (160 of 256)
     // 75 / 53, 16x16 (32) 52 / 52; FP32 1D 256 x 48^3 (576 of 1024) 93 / 87,
     // 2000 x 16^3 (500) 31 / 33; FP64 1D 2000 x 32^3 (2000 of 512) 278 / 234,
-    // 700 (704) 107 / 107, 256 (256) 36 / 45.
+    // 700 (704) 107 / 107, 256 (256) 36 / 45; FP32 3D x 16^3 24^3 cells (864 of
+    // 256, two launches) 409 / 364, 20^3 (500) 245 / 267, 40 x 24 x 12 (720) 349 / 358.
     const bool d = c->precision == BGK_FP64;
-    const double fill = c->dim == 2 ? (d ? 0.25 : 0.7) : (d ? 2.0 : 0.55), pad = d ? 1.7 : 1.35;
-    if ((double)tiles * P.npg < fill * P.slots || (double)tiles * P.tx * P.ty > pad * c->ncells) return;
+    const double fill = c->dim == 3 ? 3.3 : c->dim == 2 ? (d ? 0.25 : 0.7) : (d ? 2.0 : 0.55), pad = d ? 1.7 : 1.35;
+    if ((double)tiles * P.npg < fill * P.slots || (double)tiles * P.tx * P.ty * P.tz > pad * c->ncells) return;
     c->tile_ok = true;
     c->ntt = (int)tiles;
+    c->nti = (int)inner;
 }
 
 // p-groups are shared out over v chunks per tile: the v of the least
@@ -477,8 +485,11 @@ static int tile_chunks(const bgk_ctx *c, int vmax)
     int best = 1;
     double cost = 1e300;
     for (int v = 1; v <= std::min(P.npg, vmax); ++v) {
-        const double x = (double)c->ntt * v / P.slots;
-        const double k = x <= 4.0 ? std::ceil(x) * ((P.npg + v - 1) / v + 0.2) : (x + 0.5) * ((double)P.npg / v + 0.2);
+        double k = 0.0;
+        for (int tiles : {c->ntt - c->nti, c->nti}) {  // (3D: two launches)
+            const double x = (double)tiles * v / P.slots;
+            k += x <= 4.0 ? std::ceil(x) * ((P.npg + v - 1) / v + 0.2) : (x + 0.5) * ((double)P.npg / v + 0.2);
+        }
         if (k < cost * (1.0 - 1e-9)) {
             cost = k;
             best = v;
@@ -979,6 +990,26 @@ static void launch_tile(bgk_ctx *c, Args a, const void *src, void *dst, const re
     else go(k_tile<real, DIM, false, REC>);
 }
 
+// (boundary and inner tiles in kernels of their own: the ghosts' selection in
+// one kernel with the inner tiles' made both spill registers at every plane)
+static void launch_tile3(bgk_ctx *c, Args a, const void *src, void *dst, const float *p, hipStream_t s)
+{
+    a.vsplit = a.nparts;
+    auto go = [&](auto kern, int tiles, bool edge) {
+        a.nttiles = tiles;
+        if (tiles)
+            hipLaunchKernelGGL(kern, dim3(tiles * a.vsplit), dim3(64 * Tile3::NW), tile3_lds(c->geo, edge).total, s, a,
+                               (const float *)src, (float *)dst, p, c->partial);
+    };
+    if (stream_nt(c)) {
+        go(k_tile3<true, true>, c->ntt - c->nti, true);
+        go(k_tile3<true, false>, c->nti, false);
+    } else {
+        go(k_tile3<false, true>, c->ntt - c->nti, true);
+        go(k_tile3<false, false>, c->nti, false);
+    }
+}
+
 template <typename real>
 static int launch_stream(bgk_ctx *c, const void *src, void *dst, hipStream_t s)
 {
@@ -1046,7 +1077,8 @@ static int launch_stream(bgk_ctx *c, const void *src, void *dst, hipStream_t s)
                                (real *)dst, p, c->partial);
     } else if (use_tile(c)) {
         const real *p = (const real *)params_buf<real>(c, c->pass_parity);
-        if (c->dim == 1) launch_tile<real, 1, false>(c, make_args(c), src, dst, p, s);
+        if (c->dim == 3) launch_tile3(c, make_args(c), src, dst, (const float *)p, s);
+        else if (c->dim == 1) launch_tile<real, 1, false>(c, make_args(c), src, dst, p, s);
         else launch_tile<real, 2, false>(c, make_args(c), src, dst, p, s);
     } else if (c->dim == 3) stream_dispatch<real, 3>(c, nb, lds, src, dst, s);
     else if (c->dim == 2) stream_dispatch<real, 2>(c, nb, lds, src, dst, s);

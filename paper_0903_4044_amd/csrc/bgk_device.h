@@ -58,7 +58,8 @@ struct Inst {
     // translation-form streaming in row tiles: first tile of the instance,
     // and the sources' reach below and above a tile (cells, with a margin)
     int tile0, reach_lo, reach_hi;
-    int ttile0;     // tile streaming (k_tile): first tile of the instance
+    int ttile0;     // tile streaming (k_tile; k_tile3: tiles at a boundary): first tile of the instance
+    int itile0;     // k_tile3: first inner tile
 };
 
 // Streaming directions of an instance.

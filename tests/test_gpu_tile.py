@@ -1,4 +1,4 @@
-"""The streaming kernel on tiles of cells (k_tile) at the edges of its tiles,
+"""The streaming kernels on tiles of cells (k_tile, k_tile3) at the edges of its tiles,
 halos, lane groups and velocity chunks, against the FP64 oracle.
 
 Grids large enough for the tile kernel (its rule counts tiles times groups of
@@ -8,7 +8,9 @@ that are no multiples of 64 lanes, odd and even N_vz.
 Tolerances: FP64 every f value within 1e-12 of the largest (n steps add a few
 dozen roundings of 1.1e-16 of sums over ~1e3 velocities); FP32 moments within
 1e-5 (one unbiased rounding of 6e-8 per step, averaged over the velocities);
-the reverse step within 1e-12 of its largest entry.
+the reverse step within 1e-12 of its largest entry.  In 3D also every FP32 f
+value within 1e-6 of the largest: 3 steps of one rounding (1.2e-7) and of float
+increments of a few 6e-8 each.
 """
 import numpy as np
 import pytest
@@ -71,6 +73,21 @@ def test_tile_fp64(B, oracle_mod, probs):
 def test_tile_fp32(B, oracle_mod, kind, over):
     for v, i, ef, em in step_errors(B, oracle_mod, [prob(kind, **over)], "fp32", 4, (None, 5)):
         assert em <= 1e-5, (v, i, ef, em)
+
+
+CUBES = [[prob("cavity3d", nx=15, ny=16, nz=14, nv=(32, 32, 4), lid_mach=0.3)],
+         [prob("periodic3d", nx=16, ny=15, nz=14, nv=(32, 31, 5))],
+         [prob("cavity3d", nx=18, ny=9, nz=28, nv=(26, 28, 8), splitting="lie", limiter="none")],
+         [prob("shock", nx=7, nv=(32, 32, 4)), prob("cavity3d", nx=16, ny=16, nz=15, nv=(32, 32, 4)),
+          prob("cavity", nx=8, ny=8, nv=(32, 32, 4))]]
+
+
+@pytest.mark.parametrize("probs", CUBES)
+def test_tile_fp32_3d(B, oracle_mod, probs):
+    """Inner tiles and tiles at walls and periodic faces, sides that are no
+    multiples of 4, a batch with lower dimensions."""
+    for v, i, ef, em in step_errors(B, oracle_mod, probs, "fp32", 3, (None, 3)):
+        assert em <= 1e-5 and ef <= 1e-6, (v, i, ef, em)
 
 
 @pytest.mark.parametrize("kind,over", [FP64[0], FP64[5]])
