@@ -826,6 +826,12 @@ static Args pointwise_args(const bgk_ctx *c)
 {
     Args a = make_args(c);
     if (c->shift && c->unroll == 2) a.vsplit = std::min(c->vsplit, vsplit_for(c, 2048));
+    // where the tile kernel leaves the slots, 4096 workgroups of at least 48 KB
+    // (2304 cells x 24^3 FP64, a differentiated rollout of 6 steps 9200 us with a
+    // chunk per cell, 9015 with two; 61 x 47 x 22 x 18 x 15 FP32, 24 KB a cell, 3
+    // steps 294 with one, 300 with two)
+    const long long cell_bytes = c->geo.nv * (long long)c->esize;
+    if (use_tile(c)) a.vsplit = std::max(a.vsplit, std::min(vsplit_for(c, 4096), (int)(cell_bytes / 49152)));
     a.vsplit = std::min(a.vsplit, a.nparts);
     return a;
 }

@@ -384,11 +384,54 @@ __device__ __forceinline__ V buf_ld(__amdgpu_buffer_rsrc_t r, uint32_t voff, uin
         return __builtin_bit_cast(V, __builtin_amdgcn_raw_buffer_load_b128(r, (int)voff, (int)soff, 0));
 }
 
+// A double from another lane of the same 16-lane row (DPP move of both halves).
+template <int CTRL>
+__device__ __forceinline__ double dpp_double(double x)
+{
+    const long long b = __double_as_longlong(x);
+    const int lo = __builtin_amdgcn_update_dpp((int)b, (int)b, CTRL, 0xF, 0xF, false);
+    const int hi = __builtin_amdgcn_update_dpp((int)(b >> 32), (int)(b >> 32), CTRL, 0xF, 0xF, false);
+    return __longlong_as_double((long long)(((unsigned long long)(unsigned)hi << 32) | (unsigned)lo));
+}
+
+// A double from lane (this lane xor 16) within its 32-lane half (swizzle).
+__device__ __forceinline__ double swizzle_xor16(double x)
+{
+    constexpr int PAT = 0x1F | (0x10 << 10);  // bit mode: and 0x1F, or 0, xor 0x10
+    const long long b = __double_as_longlong(x);
+    const int lo = __builtin_amdgcn_ds_swizzle((int)b, PAT);
+    const int hi = __builtin_amdgcn_ds_swizzle((int)(b >> 32), PAT);
+    return __longlong_as_double((long long)(((unsigned long long)(unsigned)hi << 32) | (unsigned)lo));
+}
+
+// Sum over the W-lane segment of the wave that holds this lane.  Pairs of
+// lanes exchange partial sums and add them, so every lane of the segment
+// ends with the same bits: swaps within quads (DPP quad permutations), then
+// quads (half-row mirror) and half rows (row mirror) of a 16-lane row, then
+// rows through a swizzle and across the two halves through a permute.  Lanes
+// beyond a segment's data hold zeros, so a segment's sum equals that of a
+// wider one.
+template <int W = 64>
+__device__ __forceinline__ double wave_sum(double x)
+{
+    static_assert(W == 16 || W == 32 || W == 64, "segments of 16, 32 or 64 lanes");
+    x += dpp_double<0xB1>(x);   // quad_perm [1,0,3,2]
+    x += dpp_double<0x4E>(x);   // quad_perm [2,3,0,1]
+    x += dpp_double<0x141>(x);  // row_half_mirror
+    x += dpp_double<0x140>(x);  // row_mirror
+    if constexpr (W >= 32) x += swizzle_xor16(x);
+    if constexpr (W == 64) x += __shfl_xor(x, 32, 64);
+    return x;
+}
+
 // ---------------------------------------------------------------- moments
 // Partial moment sums of f over one jz chunk of one cell:
 // partial[(cell * nparts + split) * NQ + q] (without the dV factor).  Each
 // lane reads VEC consecutive jx at one jy (16-byte loads where the grid
-// allows) down its jz chunk.
+// allows) down its jz chunk.  Bound by the read of f (4.2 TB/s on large
+// grids, 5.0 with whole pages per cell); the sums meet by lane moves, not
+// through LDS, which halves the pass on small cells (18432 cells of 60
+// values 31 -> 14 us).
 template <typename real, int VEC>
 __global__ void __launch_bounds__(256) k_moments(Args A, const real *__restrict__ f, double *__restrict__ partial)
 {
@@ -431,8 +474,30 @@ __global__ void __launch_bounds__(256) k_moments(Args A, const real *__restrict_
                         e == 0 ? Azm : 0.0, e == 0 ? Azp : 0.0);
     }
     // slot (cell, split) of the A.nparts per cell the consumers add up; a
-    // launch with fewer chunks than slots zeroes the remaining ones
-    block_sum_store<NQ>(acc, partial + ((long long)gc * A.nparts + split) * NQ);
+    // launch with fewer chunks than slots zeroes the remaining ones.  The five
+    // moments, and for cells at a wall the half-range fluxes (nothing reads
+    // those of other cells)
+    const int c = gc - I.cell0, ix = c % I.nx, iy = c / I.nx % I.ny, iz = c / I.nx / I.ny;
+    const bool wall = (I.kind == KIND_CAVITY || I.kind == KIND_CAV3) &&
+                      (ix == 0 || ix == I.nx - 1 || iy == 0 || iy == I.ny - 1 ||
+                       (I.kind == KIND_CAV3 && (iz == 0 || iz == I.nz - 1)));
+    const int nq = wall ? NQ : 5;
+    __shared__ double red[4][NQ];
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, nw = (blockDim.x + 63) >> 6;
+    double mine = 0.0;
+#pragma unroll
+    for (int q = 0; q < NQ; ++q)
+        if (q < nq) {
+            const double t = wave_sum(acc[q]);
+            if (lane == q) mine = t;
+        }
+    if (lane < NQ) red[w][lane] = mine;
+    __syncthreads();
+    if (threadIdx.x < NQ) {
+        double t = 0.0;
+        for (int k = 0; k < nw; ++k) t += red[k][threadIdx.x];
+        partial[((long long)gc * A.nparts + split) * NQ + threadIdx.x] = t;
+    }
     if (split == 0)
         for (int t = threadIdx.x; t < (A.nparts - A.vsplit) * NQ; t += blockDim.x)
             partial[((long long)gc * A.nparts + A.vsplit) * NQ + t] = 0.0;
@@ -522,46 +587,6 @@ __device__ __forceinline__ void finish_relax(const Inst &I, double tau, Relax *r
     const double nu = r->n * tp / I.kn;
     r->a = -expm1(-nu * tau);
     r->P = r->n * pi_t_m32(r->T);
-}
-
-// A double from another lane of the same 16-lane row (DPP move of both halves).
-template <int CTRL>
-__device__ __forceinline__ double dpp_double(double x)
-{
-    const long long b = __double_as_longlong(x);
-    const int lo = __builtin_amdgcn_update_dpp((int)b, (int)b, CTRL, 0xF, 0xF, false);
-    const int hi = __builtin_amdgcn_update_dpp((int)(b >> 32), (int)(b >> 32), CTRL, 0xF, 0xF, false);
-    return __longlong_as_double((long long)(((unsigned long long)(unsigned)hi << 32) | (unsigned)lo));
-}
-
-// A double from lane (this lane xor 16) within its 32-lane half (swizzle).
-__device__ __forceinline__ double swizzle_xor16(double x)
-{
-    constexpr int PAT = 0x1F | (0x10 << 10);  // bit mode: and 0x1F, or 0, xor 0x10
-    const long long b = __double_as_longlong(x);
-    const int lo = __builtin_amdgcn_ds_swizzle((int)b, PAT);
-    const int hi = __builtin_amdgcn_ds_swizzle((int)(b >> 32), PAT);
-    return __longlong_as_double((long long)(((unsigned long long)(unsigned)hi << 32) | (unsigned)lo));
-}
-
-// Sum over the W-lane segment of the wave that holds this lane.  Pairs of
-// lanes exchange partial sums and add them, so every lane of the segment
-// ends with the same bits: swaps within quads (DPP quad permutations), then
-// quads (half-row mirror) and half rows (row mirror) of a 16-lane row, then
-// rows through a swizzle and across the two halves through a permute.  Lanes
-// beyond a segment's data hold zeros, so a segment's sum equals that of a
-// wider one.
-template <int W = 64>
-__device__ __forceinline__ double wave_sum(double x)
-{
-    static_assert(W == 16 || W == 32 || W == 64, "segments of 16, 32 or 64 lanes");
-    x += dpp_double<0xB1>(x);   // quad_perm [1,0,3,2]
-    x += dpp_double<0x4E>(x);   // quad_perm [2,3,0,1]
-    x += dpp_double<0x141>(x);  // row_half_mirror
-    x += dpp_double<0x140>(x);  // row_mirror
-    if constexpr (W >= 32) x += swizzle_xor16(x);
-    if constexpr (W == 64) x += __shfl_xor(x, 32, 64);
-    return x;
 }
 
 __device__ __forceinline__ int nv_of(const Geo &g, int a) { return a == 0 ? g.nvx : (a == 1 ? g.nvy : g.nvz); }
