@@ -1794,9 +1794,10 @@ __global__ void __launch_bounds__(256)
 // 64 that holds the plane) per (cell, jz chunk), 256 / W of them per
 // workgroup, no LDS and no barrier.  Such a cell is a few elements per lane,
 // and in k_shift the workgroup's set-up (v_z weights, staging, block sum) took
-// all of the time: 18432 cells x 30 x 1 x 2 FP32 43 us a pass, 11 here.  What
-// remains is the chain from the source's table entry to the segment's sum
-// (five butterflies), 9216 waves of it.
+// half of the time: 18432 cells x 30 x 1 x 2 FP32 43 us a pass, 31 here; a
+// step of 18432 cells x 8^3 113 us in row tiles, 55 here.  Bound by the
+// gathers: two sources' values and table entries, 26 loads of a cache line per
+// lane.
 template <typename real, int W, bool NTSTORE>
 __global__ void __launch_bounds__(256)
     k_shift_cells(Args A, const real *__restrict__ src, real *__restrict__ dst, const real *__restrict__ params,
