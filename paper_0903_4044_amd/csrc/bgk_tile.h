@@ -852,6 +852,8 @@ __global__ void __attribute__((amdgpu_flat_work_group_size(512, 512), amdgpu_wav
             if ((lane & 15) < NQ) acc[4 * NQ * ln + (lane & 15)] += mine;
         }
     }
+    // (lane 10 of a row completes its sum with the one that lane 9 left in LDS)
+    __syncthreads();
 #pragma unroll
     for (int ln = 0; ln < 2; ++ln) {
         const int i = tile_row_cell(lane >> 4), q = lane & 15;
