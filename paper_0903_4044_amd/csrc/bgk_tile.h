@@ -205,7 +205,15 @@ __global__ void __attribute__((amdgpu_flat_work_group_size(64 * TileShape<real, 
     const int cx0 = x0 + (DIM == 1 ? 4 * wave : 4 * (wave & 1)), cy0 = y0 + (DIM == 1 ? 0 : wave >> 1);
 #pragma unroll
     for (int i = 0; i < 4; ++i) out[i] = cy0 < I.ny && cx0 + i < I.nx;
-    const bool edge = gm != 0 || !(out[0] && out[1] && out[2] && out[3]);
+    // Tiles with cells outside the instance or, but for periodic kinds, a halo
+    // that reaches outside.  Of the whole tile and not of the wave alone: the
+    // planes' barriers then stand in control flow that the workgroup shares.
+    // (Waves of such a tile without ghosts of their own take the longer path
+    // too; they would wait for the others at each barrier.)
+    const bool per = I.kind == KIND_PER1 || I.kind == KIND_PER2;
+    const int reach = per ? 0 : 2;
+    const bool edge = x0 + S::TX + reach > I.nx || (!per && x0 == 0) ||
+                      (DIM == 2 && (y0 + S::TY + reach > I.ny || (!per && y0 == 0)));
     const bool wall = cx0 == 0 || cx0 + 4 >= I.nx || cy0 == 0 || cy0 + 1 >= I.ny;  // the wave has wall cells
     const bool xh = DIM == 2 || wave < 2;  // the wave has x-halo rows
     real c0[RPW];                           // the rows' c0 (wave-uniform)
