@@ -36,14 +36,14 @@ struct TileShape {
     // rows of a wave: four cells, YH y-halo positions (2D; the 4 TX of them
     // shared out evenly), two x-halo positions
     static constexpr int YH = DIM == 1 ? 0 : 4 * TX / NW, RPW = 4 + YH + 2, NROW = NW * RPW;
-    static constexpr int NG = 2 * TY + (DIM == 1 ? 0 : 2 * TX);  // ghost entries of a tile: left, right, bottom, top faces
+    static constexpr int NG = DIM == 1 ? 0 : 2 * TY + 2 * TX;    // wall entries of a tile: left, right, bottom, top faces
     static constexpr int NZT = NROW + NG + (NROW + NG) % 2;      // z-table columns
 };
 
 // One row of a tile: the cell whose h is read (offset in the instance, in
 // elements) and the entry that relaxes it; at a ghost position also the ghost
-// entry's z-table column and the velocities that take it (code: 0 none, 1 all,
-// 2 v_x > 0, 3 v_x <= 0, 4 v_y > 0, 5 v_y <= 0).
+// entry's z-table column and the velocities that take it (code: 0 none, 1 all
+// (k_tile3 only), 2 v_x > 0, 3 v_x <= 0, 4 v_y > 0, 5 v_y <= 0).
 struct TileRow { uint32_t off; int par, gpar, gcol, code; };
 
 template <typename real, int DIM>
@@ -155,18 +155,14 @@ __global__ void __attribute__((amdgpu_flat_work_group_size(64 * TileShape<real, 
             cx = (x % I.nx + I.nx) % I.nx;
             if (inst_dim(I) >= 2) cy = (y % I.ny + I.ny) % I.ny;
         } else if (I.kind == KIND_SHOCK) {
-            if (ox) {
-                t.gpar = I.pseudo0 + (x < 0 ? 0 : 1);
-                t.gcol = S::NROW + (x < 0 ? 0 : S::TY);
-                t.code = 1;
-            }
+            // (the far field's entry, whose c0 is 0, in place of the cell's: every velocity takes it)
         } else if (ox ? !oy && py >= 0 && py < S::TY : oy && px >= 0 && px < S::TX) {
             const int wl = ox ? (x < 0 ? 0 : 1) : (y < 0 ? 2 : 3);
             t.gpar = I.pseudo0 + wall_offset(I, wl) + (ox ? cy : cx);
             t.gcol = S::NROW + (wl == 0 ? py : wl == 1 ? S::TY + py : wl == 2 ? 2 * S::TY + px : 2 * S::TY + S::TX + px);
             t.code = wl + 2;
         }
-        t.par = I.cell0 + cy * I.nx + cx;
+        t.par = I.kind == KIND_SHOCK && ox ? I.pseudo0 + (x < 0 ? 0 : 1) : I.cell0 + cy * I.nx + cx;
         t.off = (uint32_t)(cy * I.nx + cx) * (uint32_t)g.nv;
         s_row[r] = t;
     }
@@ -200,20 +196,21 @@ __global__ void __attribute__((amdgpu_flat_work_group_size(64 * TileShape<real, 
 #pragma unroll
     for (int r = 0; r < RPW; ++r) {
         roff[r] = __builtin_amdgcn_readfirstlane(rows[r].off) * (uint32_t)sizeof(real);
-        if (__builtin_amdgcn_readfirstlane(rows[r].code)) gm |= 1 << r;
+        if (DIM == 2 && __builtin_amdgcn_readfirstlane(rows[r].code)) gm |= 1 << r;
     }
     const int cx0 = x0 + (DIM == 1 ? 4 * wave : 4 * (wave & 1)), cy0 = y0 + (DIM == 1 ? 0 : wave >> 1);
 #pragma unroll
     for (int i = 0; i < 4; ++i) out[i] = cy0 < I.ny && cx0 + i < I.nx;
-    // Tiles with cells outside the instance or, but for periodic kinds, a halo
-    // that reaches outside.  Of the whole tile and not of the wave alone: the
-    // planes' barriers then stand in control flow that the workgroup shares.
-    // (Waves of such a tile without ghosts of their own take the longer path
-    // too; they would wait for the others at each barrier.)
-    const bool per = I.kind == KIND_PER1 || I.kind == KIND_PER2;
-    const int reach = per ? 0 : 2;
-    const bool edge = x0 + S::TX + reach > I.nx || (!per && x0 == 0) ||
-                      (DIM == 2 && (y0 + S::TY + reach > I.ny || (!per && y0 == 0)));
+    // Tiles with cells outside the instance or a halo that reaches over a wall.
+    // Of the whole tile and not of the wave alone: the planes' barriers then
+    // stand in control flow that the workgroup shares.  (Waves of such a tile
+    // without ghosts of their own take the longer path too; they would wait for
+    // the others at each barrier.  One loop with the barrier between the phases'
+    // own branches spills: 128^2 x 24^3 FP32 552 us a step, 504 with this.)
+    const bool walls = I.kind == KIND_CAVITY;
+    const int reach = walls ? 2 : 0;
+    const bool edge = x0 + S::TX + reach > I.nx || (walls && x0 == 0) ||
+                      (DIM == 2 && (y0 + S::TY + reach > I.ny || (walls && y0 == 0)));
     const bool wall = cx0 == 0 || cx0 + 4 >= I.nx || cy0 == 0 || cy0 + 1 >= I.ny;  // the wave has wall cells
     const bool xh = DIM == 2 || wave < 2;  // the wave has x-halo rows
     real c0[RPW];                           // the rows' c0 (wave-uniform)
@@ -275,7 +272,7 @@ __global__ void __attribute__((amdgpu_flat_work_group_size(64 * TileShape<real, 
             yr[m] = DIM == 1 ? aw : aw + (uint32_t)((ny_ ? -k : k) * (int)(S::PITCH * RB));
         }
         auto emits = [&](int code) {
-            return code == 1 || (code == 2 && !nx_) || (code == 3 && nx_) || (code == 4 && !ny_) || (code == 5 && ny_);
+            return (code == 2 && !nx_) || (code == 3 && nx_) || (code == 4 && !ny_) || (code == 5 && ny_);
         };
         real ha[RPW];  // h of the plane in flight
         auto load = [&](real (&h)[RPW], int z) {
