@@ -865,7 +865,9 @@ __global__ void __attribute__((amdgpu_flat_work_group_size(512, 512), amdgpu_wav
         if (q < NQ && gz < I.nz && gy + ln < I.ny && x0 + i < I.nx) {
             const long long gc = I.cell0 + ((long long)gz * I.ny + gy + ln) * I.nx + x0 + i;
             const double *s = s_acc[8 * wave + 4 * ln + i];
-            partial[(gc * A.vsplit + ch) * NQ + q] = q == 10 ? s[10] + s[9] : s[q];
+            // (no plane with v_z > 0: slot 9 was never split off, all of slot 10 is its)
+            partial[(gc * A.vsplit + ch) * NQ + q] = q < 9 ? s[q] : g.zneg < g.nvz ? (q == 10 ? s[10] + s[9] : s[9])
+                                                     : q == 9 ? -s[10] : 0.0;
         }
     }
 }

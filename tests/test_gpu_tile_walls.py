@@ -57,3 +57,13 @@ def check(B, oracle_mod, cfg, f0, n, chunks):
 def test_flow_onto_the_z_walls(B, oracle_mod, u):
     cfg = prob("cavity3d", nx=16, ny=16, nz=15, nv=(32, 32, 8), lid_mach=0.3)
     check(B, oracle_mod, cfg, u, 3, (None, 1, 3))
+
+
+@pytest.mark.parametrize("lo,hi,u", [((-3.0, -3.0, -4.0), (3.0, 3.0, -0.5), -2.0), ((-3.0, -3.0, 0.5), (3.0, 3.0, 4.0), 2.0),
+                                     ((0.5, -3.0, -3.0), (4.0, 3.0, 3.0), 0.0), ((-3.0, -4.0, -3.0), (3.0, -0.5, 3.0), 0.0)])
+def test_one_sided_boxes(B, oracle_mod, lo, hi, u):
+    """Velocity boxes on one side of v = 0 along an axis: one half-range flux
+    is the whole sum, the other is zero, and the wall that it feeds emits
+    nothing."""
+    cfg = prob("cavity3d", nx=16, ny=15, nz=16, nv=(32, 32, 4), vlo=lo, vhi=hi)
+    check(B, oracle_mod, cfg, u, 3, (None, 1, 3))
