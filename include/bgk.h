@@ -251,6 +251,11 @@ int bgk_autotune(bgk_ctx *ctx, const void *f, void *scratch, void *ws, void *str
 int bgk_get_launch(const bgk_ctx *ctx, int *vec, int *unroll, int *vsplit, int *persist, double *tuned_us);
 int bgk_set_launch(bgk_ctx *ctx, int vec, int unroll, int vsplit, int persist);
 
+/* Name of the streaming kernel that the shape in use runs, a static string:
+ * k_stream (per cell), k_tile or k_tile3 (on tiles of cells; 1D and 2D, 3D
+ * kinds), k_shift, k_shift_cells or k_shift_rows (translation form). */
+int bgk_get_kernel(const bgk_ctx *ctx, const char **name);
+
 /* Graph replay.  When on (default off), bgk_step captures every launch of
  * the call after the one that sets the rounding counter (moments of f_in,
  * tables, all n_steps streaming passes and tables, closing relaxation) into

@@ -51,7 +51,7 @@ class Problem(ctypes.Structure):
 
 EXPORTS = ("bgk_init", "bgk_free", "bgk_last_error", "bgk_sizes", "bgk_instance_info",
            "bgk_initial_state", "bgk_step", "bgk_moments", "bgk_check", "bgk_set_timing",
-           "bgk_timing", "bgk_autotune", "bgk_get_launch", "bgk_set_launch", "bgk_set_graph",
+           "bgk_timing", "bgk_autotune", "bgk_get_launch", "bgk_get_kernel", "bgk_set_launch", "bgk_set_graph",
            "bgk_step_adjoint", "bgk_lid_shear", "bgk_lid_shear_grad", "bgk_set_rounding_seed",
            "bgk_get_rounding_seed", "bgk_cavity_metrics", "bgk_step_noalloc", "bgk_record_bytes",
            "bgk_step_record", "bgk_step_adjoint_record", "bgk_adjoint_sweep_record")
@@ -87,6 +87,7 @@ def load(path: str = LIB_PATH):
     L.bgk_timing.argtypes = [vp, dp, ip]
     L.bgk_autotune.argtypes = [vp, vp, vp, vp, vp]
     L.bgk_get_launch.argtypes = [vp, ip, ip, ip, ip, dp]
+    L.bgk_get_kernel.argtypes = [vp, ctypes.POINTER(ctypes.c_char_p)]
     L.bgk_set_launch.argtypes = [vp, ctypes.c_int, ctypes.c_int, ctypes.c_int, ctypes.c_int]
     L.bgk_set_graph.argtypes = [vp, ctypes.c_int]
     L.bgk_step_adjoint.argtypes = [vp, vp, vp, vp, vp, vp, vp]
@@ -372,6 +373,12 @@ class Context:
         self._check(self.L.bgk_get_launch(self.h, ctypes.byref(v), ctypes.byref(u), ctypes.byref(s), ctypes.byref(p),
                                           ctypes.byref(us)))
         return {"vec": v.value, "unroll": u.value, "vsplit": s.value, "persist": p.value, "tuned_us": us.value}
+
+    def kernel(self) -> str:
+        """Name of the streaming kernel that the shape in use runs."""
+        name = ctypes.c_char_p()
+        self._check(self.L.bgk_get_kernel(self.h, ctypes.byref(name)))
+        return name.value.decode()
 
     def set_launch(self, vec: int, unroll: int, vsplit: int, persist: int = 0):
         self._check(self.L.bgk_set_launch(self.h, int(vec), int(unroll), int(vsplit), int(persist)))

@@ -1891,6 +1891,15 @@ extern "C" int bgk_get_launch(const bgk_ctx *ctx, int *vec, int *unroll, int *vs
     return BGK_OK;
 }
 
+extern "C" int bgk_get_kernel(const bgk_ctx *ctx, const char **name)
+{
+    if (!ctx || !name) return BGK_E_INVALID;
+    if (ctx->shift) *name = ctx->unroll == 2 ? "k_shift_rows" : ctx->geo.npl <= 64 ? "k_shift_cells" : "k_shift";
+    else if (use_tile(ctx)) *name = ctx->dim == 3 ? "k_tile3" : "k_tile";
+    else *name = "k_stream";
+    return BGK_OK;
+}
+
 extern "C" int bgk_set_launch(bgk_ctx *ctx, int vec, int unroll, int vsplit, int persist)
 {
     if (!ctx) return BGK_E_INVALID;

@@ -29,8 +29,8 @@ def B():
 
 RED = dict(nv=(26, 28, 2), vlo=(-3.0, -3.0, -1.0), vhi=(3.0, 3.0, 1.0), reduced=True)
 CASES = [("cavity", dict(nx=41, ny=39, nv=(26, 28, 5))),
-         ("cavity", dict(nx=42, ny=33, nv=(26, 28, 4), splitting="lie", limiter="none", lid_mach=-0.3)),
-         ("cavity", dict(nx=34, ny=41, nv=(26, 28, 6), maxwellian="conservative")),
+         ("cavity", dict(nx=44, ny=33, nv=(26, 28, 4), splitting="lie", limiter="none", lid_mach=-0.3)),
+         ("cavity", dict(nx=36, ny=41, nv=(26, 28, 6), maxwellian="conservative")),
          ("cavity", dict(nx=43, ny=47, **RED)), ("periodic2d", dict(nx=39, ny=42, nv=(26, 28, 4))),
          ("shock", dict(nx=1401, nv=(26, 28, 5))), ("periodic1d", dict(nx=1403, nv=(28, 26, 4)))]
 
@@ -42,6 +42,7 @@ def test_edge_tiles_fp32(B, oracle_mod, kind, over):
     f0 = initial(O, seed=70)
     ref = O.step(f0, 3)
     C = B.Context(cfg, "fp32", tune="off")
+    assert C.kernel() == "k_tile"
     x = torch.tensor(f0.reshape(-1), dtype=torch.float32, device="cuda")
     for v in (None, 1, 2):
         if v is not None:
@@ -56,6 +57,7 @@ def test_edge_tiles_record_fp32(B, oracle_mod, kind, over):
     cfg = prob(kind, **over)
     O = oracle_mod.Oracle(cfg)
     C = B.Context(cfg, "fp32", tune="off")
+    assert C.kernel() == "k_tile"
     f0 = initial(O, seed=71)
     lam = inputs.uniform(O.shape, seed=72, lo=-1, hi=1)
     dev = lambda a: torch.tensor(a.reshape(-1), dtype=torch.float32, device="cuda")

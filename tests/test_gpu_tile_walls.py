@@ -40,6 +40,7 @@ def check(B, oracle_mod, cfg, f0, n, chunks):
     assert np.isfinite(ref).all()
     rm = O.moments(ref)
     C = B.Context(cfg, "fp32", tune="off")
+    assert C.kernel() == "k_tile3"
     x = torch.tensor(f0.reshape(-1), dtype=torch.float32, device="cuda")
     for v in chunks:
         if v is not None:
