@@ -38,7 +38,8 @@ struct bgk_ctx {
     int ncells = 0, npseudo = 0;
     size_t f_elems = 0;
     int vsplit = 1;            // jz chunks per cell (one workgroup each)
-    int vsplit_max = 1;        // largest vsplit the partial-sum buffer holds
+    int vsplit_max = 1;        // largest chunk count the partial-sum buffer holds
+    int cell_vmax = 1;         // the per-cell kernels' largest (tiles may take more)
     int vec = 1;               // streaming kernel: jx per lane task
     int zr = 1;                // streaming kernel: jz residues per workgroup
     int sblock = 256;          // streaming kernel: threads per workgroup
@@ -137,6 +138,8 @@ static int kind_dim(int k)
 // per cell it leaves.
 static bool use_tile(const bgk_ctx *c) { return c->tile_ok && c->vec == 1; }
 static int num_parts(const bgk_ctx *c) { return use_tile(c) ? c->tsplit : c->vsplit; }
+// Largest vsplit of the shape's kernel.
+static int max_chunks(const bgk_ctx *c) { return use_tile(c) ? c->vsplit_max : c->cell_vmax; }
 
 static Args make_args(const bgk_ctx *c)
 {
@@ -363,13 +366,13 @@ static void set_shape(bgk_ctx *c, int vec, int unroll, int vsplit, int persist =
     c->vec = vec;
     c->unroll = unroll;
     c->persist = persist;
-    c->vsplit = std::max(1, std::min(c->vsplit_max, vsplit));
+    c->vsplit = std::max(1, std::min(max_chunks(c), vsplit));
     if (c->shift && unroll == 2) c->vsplit = g.nvz;  // row tiles: one plane per work item
     if (use_tile(c)) {
         // the shape's chunks are the tiles' p-group chunks; the per-cell kernels
         // (moments, closing relaxation, reverse sweep) keep jz chunks of their own
         c->tsplit = c->vsplit;
-        c->vsplit = std::min(c->vsplit_max, default_vsplit(c));
+        c->vsplit = std::min(c->cell_vmax, default_vsplit(c));
     }
     task_shape(g, c->vec, g.nvz / c->vsplit, &c->zr, &c->sblock);
 }
@@ -505,6 +508,7 @@ static void choose_launch(bgk_ctx *c, bool keep_scratch)
     // the y-neighbour rows of the cells in flight resident in each XCD's L2
     c->vsplit_max = std::max(vsplit_for(c, 8192), std::min(c->geo.nvz, 4));
     if (c->row_ok) c->vsplit_max = std::max(c->vsplit_max, c->geo.nvz);
+    c->cell_vmax = c->vsplit_max;
     // (keep_scratch: no more partial sums than the per-cell kernel takes)
     const int tile_vmax = keep_scratch ? c->vsplit_max : NVMAX * NVMAX / 64;
     int vec = 1;
@@ -1809,11 +1813,11 @@ static int autotune(bgk_ctx *c, const void *f, void *tmp, hipStream_t s)
     std::vector<Cand> cands;
     std::vector<int> splits;
     for (int t : {256, 512, 1024, 2048, 4096, 8192}) {
-        const int v = std::min(vsplit_for(c, t), c->vsplit_max);
+        const int v = std::min(vsplit_for(c, t), c->cell_vmax);
         if (std::find(splits.begin(), splits.end(), v) == splits.end()) splits.push_back(v);
     }
     for (int v : {2, 4})
-        if (v <= c->vsplit_max && std::find(splits.begin(), splits.end(), v) == splits.end()) splits.push_back(v);
+        if (v <= c->cell_vmax && std::find(splits.begin(), splits.end(), v) == splits.end()) splits.push_back(v);
     auto measure = [&](const Cand &k, double *us, int n, int warm) {
         set_shape(c, k.vec, k.unroll, k.vsplit, k.persist);
         return time_steps<real>(c, f, tmp, s, us, n, warm);
@@ -1904,8 +1908,8 @@ extern "C" int bgk_set_launch(bgk_ctx *ctx, int vec, int unroll, int vsplit, int
 {
     if (!ctx) return BGK_E_INVALID;
     if (!(vec == 1 || vec == 2 || vec == 4) || !vec_valid(ctx, vec) || unroll < 1 || unroll > 4 ||
-        (ctx->shift && unroll > (ctx->row_ok ? 2 : 1)) || (ctx->dim == 3 && unroll > 2) || vsplit < 1 || vsplit > ctx->vsplit_max ||
-        persist < 0 || persist > 64)
+        (ctx->shift && unroll > (ctx->row_ok ? 2 : 1)) || (ctx->dim == 3 && unroll > 2) || vsplit < 1 ||
+        vsplit > (ctx->tile_ok && vec == 1 ? ctx->vsplit_max : ctx->cell_vmax) || persist < 0 || persist > 64)
         return fail(ctx, BGK_E_INVALID, "bgk_set_launch: shape not valid for this context");
     set_shape(ctx, vec, unroll, vsplit, persist);
     return BGK_OK;
