@@ -228,8 +228,9 @@ int bgk_check(bgk_ctx *ctx, const void *f, void *stream);
  * per work item, k > 0 launches k workgroups per compute unit that walk the
  * items of all instances (one persistent launch for a batch).  Where there
  * are enough cells to fill the device with tiles of them (3D kinds: BGK_FP32
- * only), vec 1 is the kernel on tiles: vsplit then counts chunks of (jx,
- * jy) groups per tile, unroll and persist have no effect.  Vec is 1
+ * only), (1, 1, vsplit, 0) is the kernel on tiles, vsplit counting chunks of
+ * (jx, jy) groups per tile; every other shape is the per-cell kernel there
+ * as elsewhere (bgk_get_kernel tells which runs).  Vec is 1
  * for BGK_SHIFT streaming, reduced velocity spaces and 3D kinds; 3D kinds
  * take unroll 1 or 2.  BGK_SHIFT contexts take unroll 1 (the per-cell
  * translation kernel) or, where its row tiles fit, 2 (the row-tile kernel).

@@ -45,8 +45,8 @@ struct bgk_ctx {
     int sblock = 256;          // streaming kernel: threads per workgroup
     int unroll = 1;            // streaming kernel: jz values whose loads are issued together
     int persist = 0;           // streaming kernel: 0 one workgroup per item, else resident workgroups per CU
-    // tile streaming (k_tile, the shape's vec = 1 where it fits): tiles over all
-    // instances, chunks of p-groups per tile
+    // tile streaming (k_tile, the shape (1, 1, chunks, 0) where it fits): tiles
+    // over all instances, chunks of p-groups per tile
     bool tile_ok = false;
     int ntt = 0, nti = 0, tsplit = 1;
     bool shift = false;        // every instance streams in the translation form (k_shift)
@@ -135,8 +135,14 @@ static int kind_dim(int k)
 }
 
 // Does the streaming pass run on tiles of cells, and the partial moment sums
-// per cell it leaves.
-static bool use_tile(const bgk_ctx *c) { return c->tile_ok && c->vec == 1; }
+// per cell it leaves.  The pipelines and persistent grids of vec = 1 stay the
+// per-cell kernel's, which has no other shape on odd N_vx, in reduced spaces
+// and in 3D.
+static bool tile_shape(const bgk_ctx *c, int vec, int unroll, int persist)
+{
+    return c->tile_ok && vec == 1 && unroll == 1 && persist == 0;
+}
+static bool use_tile(const bgk_ctx *c) { return tile_shape(c, c->vec, c->unroll, c->persist); }
 static int num_parts(const bgk_ctx *c) { return use_tile(c) ? c->tsplit : c->vsplit; }
 // Largest vsplit of the shape's kernel.
 static int max_chunks(const bgk_ctx *c) { return use_tile(c) ? c->vsplit_max : c->cell_vmax; }
@@ -525,7 +531,7 @@ static void choose_launch(bgk_ctx *c, bool keep_scratch)
     if (c->tile_ok) {
         const int v = tile_chunks(c, tile_vmax);
         c->vsplit_max = std::max(c->vsplit_max, v);
-        vec = 1;
+        vec = unroll = 1;
         vsplit = v;
     }
     set_shape(c, vec, unroll, vsplit);
@@ -1829,16 +1835,14 @@ static int autotune(bgk_ctx *c, const void *f, void *tmp, hipStream_t s)
         for (int r = 0; r < 3 && !rc; ++r) rc = time_steps<real>(c, f, tmp, s, &us);
     }
     std::vector<int> tsplits;  // chunks of p-groups per tile
-    for (int v : {1, 2, 3, 4, 6, 9, 12, 18, start.vsplit})
+    for (int v : {1, 2, 3, 4, 6, 9, 12, 18, tile_shape(c, start.vec, start.unroll, start.persist) ? start.vsplit : 1})
         if (v <= c->vsplit_max && std::find(tsplits.begin(), tsplits.end(), v) == tsplits.end()) tsplits.push_back(v);
     for (int vec : {4, 2, 1}) {
         if (!vec_valid(c, vec)) continue;
-        const bool tile = c->tile_ok && vec == 1;  // one kernel, a plain grid
         for (int unroll : {1, 2, 3, 4})
-            for (int vs : tile ? tsplits : splits)
-                for (int ps : {0, 2, 4}) {
+            for (int ps : {0, 2, 4})
+                for (int vs : tile_shape(c, vec, unroll, ps) ? tsplits : splits) {
                     if (rc) break;
-                    if (tile && (unroll > 1 || ps)) continue;
                     if (c->shift && unroll > (c->row_ok ? 2 : 1)) continue;  // per-cell or row tiles
                     if (c->dim == 3 && unroll > 2) continue;  // 3D: modes 1 and 2 only
                     if (ps && c->ncells * vs <= ps * c->ncu) continue;  // grid already resident
@@ -1909,7 +1913,7 @@ extern "C" int bgk_set_launch(bgk_ctx *ctx, int vec, int unroll, int vsplit, int
     if (!ctx) return BGK_E_INVALID;
     if (!(vec == 1 || vec == 2 || vec == 4) || !vec_valid(ctx, vec) || unroll < 1 || unroll > 4 ||
         (ctx->shift && unroll > (ctx->row_ok ? 2 : 1)) || (ctx->dim == 3 && unroll > 2) || vsplit < 1 ||
-        vsplit > (ctx->tile_ok && vec == 1 ? ctx->vsplit_max : ctx->cell_vmax) || persist < 0 || persist > 64)
+        vsplit > (tile_shape(ctx, vec, unroll, persist) ? ctx->vsplit_max : ctx->cell_vmax) || persist < 0 || persist > 64)
         return fail(ctx, BGK_E_INVALID, "bgk_set_launch: shape not valid for this context");
     set_shape(ctx, vec, unroll, vsplit, persist);
     return BGK_OK;
