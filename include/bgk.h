@@ -233,7 +233,8 @@ int bgk_check(bgk_ctx *ctx, const void *f, void *stream);
  * as elsewhere (bgk_get_kernel tells which runs).  Vec is 1
  * for BGK_SHIFT streaming, reduced velocity spaces and 3D kinds; 3D kinds
  * take unroll 1 or 2.  BGK_SHIFT contexts take unroll 1 (the per-cell
- * translation kernel) or, where its row tiles fit, 2 (the row-tile kernel).
+ * translation kernel; on planes of at most 64 values persist has no effect)
+ * or, where its row tiles fit, 2 (the row-tile kernel).
  * bgk_init picks a default.  bgk_autotune times every valid shape on the
  * state f (device, f_elems elements, read only; synchronises the stream) and
  * keeps the fastest by the steady time of a real step (streaming pass and

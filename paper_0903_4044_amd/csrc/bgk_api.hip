@@ -1845,6 +1845,7 @@ static int autotune(bgk_ctx *c, const void *f, void *tmp, hipStream_t s)
                     if (rc) break;
                     if (c->shift && unroll > (c->row_ok ? 2 : 1)) continue;  // per-cell or row tiles
                     if (c->dim == 3 && unroll > 2) continue;  // 3D: modes 1 and 2 only
+                    if (ps && c->shift && unroll == 1 && c->geo.npl <= 64) continue;  // k_shift_cells: a plain grid
                     if (ps && c->ncells * vs <= ps * c->ncu) continue;  // grid already resident
                     Cand k{0.0, vec, unroll, vs, ps};
                     rc = measure(k, &k.us, 8, 0);

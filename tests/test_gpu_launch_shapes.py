@@ -61,3 +61,13 @@ def test_persistent_batch_is_persistent(B):  # noqa: F811
     assert C.kernel() == "k_tile"
     C.set_launch(s["vec"], s["unroll"], min(s["vsplit"], 4), 2)
     assert C.kernel() == "k_stream" and C.launch()["persist"] == 2
+
+
+def test_tuner_gives_small_translation_planes_no_persistent_grid(B):  # noqa: F811
+    """k_shift_cells launches a plain grid whatever persist says: the tuner
+    neither times such shapes again nor reports one."""
+    C = B.Context(prob("shock", nx=3000, limiter="shift", splitting="lie", nv=(30, 1, 2), reduced=True,
+                       vlo=(-4.0, -1.0, -1.0), vhi=(4.0, 1.0, 1.0)), "fp32", tune="off")
+    for _ in range(3):
+        s = C.autotune(C.initial_state())
+        assert C.kernel() == "k_shift_rows" or s["persist"] == 0
