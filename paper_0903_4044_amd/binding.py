@@ -133,9 +133,10 @@ def to_struct(cfg: dict) -> Problem:
 
 
 def size_class(problems, precision: str) -> str:
-    """Key of the tuned-shape table: dimension (the highest of a batch that
-    mixes them), precision, velocity grid and the power-of-two bucket of the
-    total cell count."""
+    """Size class of the tuned-shape table (its key adds the context's
+    streaming form): dimension (the highest of a batch that mixes them),
+    precision, velocity grid and the power-of-two bucket of the total cell
+    count."""
     import math
     p0 = problems[0]
     cells = sum(inputs.ncells(p) for p in problems)
@@ -143,6 +144,26 @@ def size_class(problems, precision: str) -> str:
     nv = "x".join(str(int(v)) for v in p0["nv"])
     dim = max(inputs.ndim(p) for p in problems)
     return f"{dim}d/{precision}/nv{nv}/cells<={bucket}"
+
+
+# Streaming form of a context, from the kernel of its default shape: on tiles
+# of cells, per cell, translation.
+FORMS = {"k_tile": "tiles", "k_tile3": "tiles", "k_stream": "cells", "k_shift": "shift", "k_shift_cells": "shift",
+         "k_shift_rows": "shift"}
+
+
+def tuned_shape(table: dict, key: str, form: str) -> dict | None:
+    """The recorded launch shape of a size class for a context of this form.
+    An entry without a form, from a table saved before the key held it, serves
+    every form that accepts it, except where it reads (1, 1, vsplit, 0): that
+    counts jz chunks or lane-group chunks of tiles, and such an entry does not
+    say which."""
+    shape = table.get(f"{key}/{form}")
+    if shape is None:
+        shape = table.get(key)
+        if shape and (shape["vec"], shape["unroll"], shape.get("persist", 0)) == (1, 1, 0):
+            shape = None
+    return shape
 
 
 def load_tuned() -> dict:
@@ -183,8 +204,8 @@ def step_noalloc(problems, precision: str, f_in: torch.Tensor, f_out: torch.Tens
 class Context:
     """Owns a bgk_ctx for one or more instances stepped together.
 
-    tune: "table" applies the launch shape recorded for this size class in
-    tuned.json (if any), "off" keeps the library default; call autotune() to
+    tune: "table" applies the launch shape recorded for this size class and
+    streaming form in tuned.json (if any), "off" keeps the library default; call autotune() to
     time all shapes on the current device.
     """
 
@@ -220,10 +241,11 @@ class Context:
             self.cell_offsets.append(co.value)
             self.dts.append(dt.value)
         self.key = size_class(self.problems, self.precision)
+        self.form = FORMS[self.kernel()]
         if tune == "table":
-            shape = load_tuned().get(self.key)
+            shape = tuned_shape(load_tuned(), self.key, self.form)
             if shape:
-                try:  # a shape recorded for another streaming form of the same size class may not apply
+                try:  # a shape of another device or, without a form, of another kernel may not apply
                     self.set_launch(shape["vec"], shape["unroll"], shape["vsplit"], shape.get("persist", 0))
                 except BGKError:
                     pass

@@ -44,9 +44,10 @@ def main() -> int:
         f = ctx.initial_state()
         torch.cuda.synchronize()
         shape = ctx.autotune(f)
-        table[ctx.key] = {k: shape[k] for k in ("vec", "unroll", "vsplit", "persist")} | {"us": round(shape["tuned_us"], 2),
+        key = f"{ctx.key}/{ctx.form}"
+        table[key] = {k: shape[k] for k in ("vec", "unroll", "vsplit", "persist")} | {"us": round(shape["tuned_us"], 2),
                                                                                 "workload": name}
-        print(f"{name}: {ctx.key} -> {table[ctx.key]}", flush=True)
+        print(f"{name}: {key} -> {table[key]}", flush=True)
         del f
         ctx.close()
         torch.cuda.empty_cache()
