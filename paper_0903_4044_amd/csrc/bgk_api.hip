@@ -507,16 +507,40 @@ static int tile_chunks(const bgk_ctx *c, int vmax)
     return best;
 }
 
+// Device data of an allocation-free step (bgk_step_noalloc) with partial sums
+// for v chunks: instances, cell and ghost prefixes, table entries of both
+// parities, partial sums, rounding counter, each 256-byte aligned.
+constexpr size_t NOALLOC_SCRATCH_BYTES = (size_t)BGK_NOALLOC_SCRATCH_MIB << 20;
+
+struct ScratchLayout { size_t inst, prefix, params, partial, pass, total; };
+
+static ScratchLayout scratch_layout(const bgk_ctx *c, int v)
+{
+    auto up = [](size_t x) { return (x + 255) & ~(size_t)255; };
+    ScratchLayout L;
+    L.inst = up(sizeof(Inst) * c->ninst);
+    L.prefix = up(sizeof(int) * (c->ninst + 1));
+    L.params = up(2 * (size_t)(c->ncells + c->npseudo) * c->geo.pe * c->esize);
+    L.partial = up(sizeof(double) * (size_t)c->ncells * v * NQ);
+    L.pass = 256;
+    L.total = L.inst + 2 * L.prefix + L.params + L.partial + L.pass;
+    return L;
+}
+
 // Default shape (measured on MI355X for the paper's grids; bgk_autotune refines it).
-static void choose_launch(bgk_ctx *c, bool keep_scratch)
+static void choose_launch(bgk_ctx *c)
 {
     // up to 4 jz chunks per cell even on large grids: smaller work items keep
     // the y-neighbour rows of the cells in flight resident in each XCD's L2
     c->vsplit_max = std::max(vsplit_for(c, 8192), std::min(c->geo.nvz, 4));
     if (c->row_ok) c->vsplit_max = std::max(c->vsplit_max, c->geo.nvz);
     c->cell_vmax = c->vsplit_max;
-    // (keep_scratch: no more partial sums than the per-cell kernel takes)
-    const int tile_vmax = keep_scratch ? c->vsplit_max : NVMAX * NVMAX / 64;
+    // Chunks of tiles: any number, but where an allocation-free step has room for
+    // the per-cell kernel's partial sums, no more than it has room for (that call
+    // and a context take the same shape, and no problem loses the call to tiles).
+    int tile_vmax = NVMAX * NVMAX / 64;
+    if (scratch_layout(c, c->cell_vmax).total <= NOALLOC_SCRATCH_BYTES)
+        while (tile_vmax > c->cell_vmax && scratch_layout(c, tile_vmax).total > NOALLOC_SCRATCH_BYTES) --tile_vmax;
     int vec = 1;
     for (int v : {4, 2})
         if (vec_valid(c, v)) { vec = v; break; }
@@ -540,8 +564,7 @@ static void choose_launch(bgk_ctx *c, bool keep_scratch)
 // Host-side set-up of a context: validation, geometry, instance tables,
 // time steps and the default launch shape.  No device memory is touched.
 // Returns a status code and sets msg on failure.
-static int plan_ctx(const bgk_problem *probs, int n_probs, int precision, bgk_ctx *c, std::string &msg,
-                    bool keep_scratch = false)
+static int plan_ctx(const bgk_problem *probs, int n_probs, int precision, bgk_ctx *c, std::string &msg)
 {
     if (!probs || n_probs < 1) {
         msg = "need at least one problem";
@@ -702,7 +725,7 @@ static int plan_ctx(const bgk_problem *probs, int n_probs, int precision, bgk_ct
     if (c->shift) plan_rows(c);
     plan_tile(c);
 
-    choose_launch(c, keep_scratch);
+    choose_launch(c);
     return BGK_OK;
 }
 
@@ -2048,7 +2071,6 @@ extern "C" int bgk_timing(bgk_ctx *ctx, double *ms, int *launches)
 // NOALLOC_SCRATCH_BYTES; each device holds its own copy until the process
 // ends.  Host code never passes the array's name to a kernel: its device
 // address comes from hipGetSymbolAddress, once per device.
-constexpr size_t NOALLOC_SCRATCH_BYTES = (size_t)BGK_NOALLOC_SCRATCH_MIB << 20;
 static __device__ __align__(256) unsigned char scratch[NOALLOC_SCRATCH_BYTES];
 
 static std::mutex g_scratch_mu;
@@ -2103,18 +2125,13 @@ extern "C" int bgk_step_noalloc(const bgk_problem *probs, int n_probs, int preci
 {
     bgk_ctx c;  // host-side plan; its device pointers are carved from the scratch array
     std::string msg;
-    int rc = plan_ctx(probs, n_probs, precision, &c, msg, true);
+    int rc = plan_ctx(probs, n_probs, precision, &c, msg);
     if (rc) return fail(nullptr, rc, msg);
-    // layout of the scratch array, 256-byte aligned pieces
-    auto up = [](size_t x) { return (x + 255) & ~(size_t)255; };
-    const size_t b_inst = up(sizeof(Inst) * n_probs), b_pre = up(sizeof(int) * (n_probs + 1));
-    const size_t b_par = up(2 * (size_t)(c.ncells + c.npseudo) * c.geo.pe * c.esize);
-    const size_t b_part = up(sizeof(double) * (size_t)c.ncells * c.vsplit_max * NQ), b_pass = 256;
-    const size_t total = b_inst + 2 * b_pre + b_par + b_part + b_pass;
-    if (total > NOALLOC_SCRATCH_BYTES) {
+    const ScratchLayout L = scratch_layout(&c, c.vsplit_max);
+    if (L.total > NOALLOC_SCRATCH_BYTES) {
         char b[200];
         snprintf(b, sizeof b, "bgk_step_noalloc: the problems need %.1f MiB of device scratch; the static array holds %d MiB",
-                 (double)total / (1 << 20), BGK_NOALLOC_SCRATCH_MIB);
+                 (double)L.total / (1 << 20), BGK_NOALLOC_SCRATCH_MIB);
         return fail(nullptr, BGK_E_UNSUPPORTED, b);
     }
     if (!f_in || !f_out) return fail(nullptr, BGK_E_INVALID, "bgk_step_noalloc: NULL buffer");
@@ -2136,15 +2153,15 @@ extern "C" int bgk_step_noalloc(const bgk_problem *probs, int n_probs, int preci
     if (rc) return fail(nullptr, rc, msg);
     unsigned char *q = (unsigned char *)base;
     c.d_inst = (Inst *)q;
-    q += b_inst;
+    q += L.inst;
     c.d_cell_prefix = (int *)q;
-    q += b_pre;
+    q += L.prefix;
     c.d_pseudo_prefix = (int *)q;
-    q += b_pre;
+    q += L.prefix;
     c.params = q;
-    q += b_par;
+    q += L.params;
     c.partial = (double *)q;
-    q += b_part;
+    q += L.partial;
     c.pass = (uint32_t *)q;
     rc = upload(c.h_inst.data(), sizeof(Inst) * n_probs, c.d_inst, s, msg);
     if (!rc) rc = upload(c.h_cell_prefix.data(), sizeof(int) * (n_probs + 1), c.d_cell_prefix, s, msg);

@@ -56,10 +56,12 @@ struct Inst {
     double x0, dx;  // spatial origin and cell size along x
     double up[3], dn[3];  // shock far-field (n, V, T)
     // translation-form streaming in row tiles: first tile of the instance,
-    // and the sources' reach below and above a tile (cells, with a margin)
-    int tile0, reach_lo, reach_hi;
-    int ttile0;     // tile streaming (k_tile; k_tile3: tiles at a boundary): first tile of the instance
-    int itile0;     // k_tile3: first inner tile
+    // and the sources' reach below and above a tile (cells, with a margin);
+    // streaming on tiles of cells, which no such context has: first tile of the
+    // instance (k_tile; k_tile3: tiles at a boundary), first inner tile (k_tile3)
+    union { int tile0, ttile0; };
+    union { int reach_lo, itile0; };
+    int reach_hi;
 };
 
 // Streaming directions of an instance.
