@@ -853,26 +853,27 @@ static int pointwise_block(const bgk_ctx *c) { return fit_block(c->geo.npl / poi
 // Arguments of the pointwise kernels (moments, initial state, closing
 // relaxation): their own jz chunk count, the streaming one except for the
 // row-tile translation form, whose one chunk per plane would leave these
-// kernels mostly empty workgroups; the moment sums still fill every one of
-// the nparts slots per cell that the table preparation adds up.
+// kernels mostly empty workgroups.
 static Args pointwise_args(const bgk_ctx *c)
 {
     Args a = make_args(c);
     if (c->shift && c->unroll == 2) a.vsplit = std::min(c->vsplit, vsplit_for(c, 2048));
-    // where the tile kernel leaves the slots, 4096 workgroups of at least 48 KB
+    // beside the tile kernel, 4096 workgroups of at least 48 KB
     // (2304 cells x 24^3 FP64, a differentiated rollout of 6 steps 9200 us with a
     // chunk per cell, 9015 with two; 61 x 47 x 22 x 18 x 15 FP32, 24 KB a cell, 3
     // steps 294 with one, 300 with two)
     const long long cell_bytes = c->geo.nv * (long long)c->esize;
     if (use_tile(c)) a.vsplit = std::max(a.vsplit, std::min(vsplit_for(c, 4096), (int)(cell_bytes / 49152)));
-    a.vsplit = std::min(a.vsplit, a.nparts);
     return a;
 }
 
 template <typename real>
 static int launch_moments(bgk_ctx *c, const void *f, hipStream_t s)
 {
-    const Args a = pointwise_args(c);
+    // (the sums fill the nparts slots per cell that the table preparation adds
+    // up: tiles may leave fewer than the chunks of a pointwise pass)
+    Args a = pointwise_args(c);
+    a.vsplit = std::min(a.vsplit, a.nparts);
     const int nb = c->ncells * a.vsplit;
     if (pointwise_vec(c) == 4)
         hipLaunchKernelGGL((k_moments<real, 4>), dim3(nb), dim3(pointwise_block(c)), 0, s, a, (const real *)f, c->partial);

@@ -71,3 +71,16 @@ def test_tuner_gives_small_translation_planes_no_persistent_grid(B):  # noqa: F8
     for _ in range(3):
         s = C.autotune(C.initial_state())
         assert C.kernel() == "k_shift_rows" or s["persist"] == 0
+
+
+def test_entry_and_exit_passes_do_not_follow_the_tiles_chunks(B):  # noqa: F811
+    """The initial state and the closing relaxation write no partial sums:
+    neither depends on how many chunks the tiles leave."""
+    C = B.Context(prob("cavity", nx=26, ny=25, nv=(14, 11, 5), maxwellian="conservative"), "fp64", tune="off")
+    assert C.kernel() == "k_tile"
+    ref = C.initial_state()
+    y = C.step(ref, n=1)
+    for v in (1, 2):
+        C.set_launch(1, 1, v, 0)
+        assert torch.equal(C.initial_state(), ref)
+        assert float((C.step(ref, n=1) - y).abs().max()) <= 1e-12 * float(y.abs().max())
