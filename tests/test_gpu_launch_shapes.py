@@ -84,3 +84,13 @@ def test_entry_and_exit_passes_do_not_follow_the_tiles_chunks(B):  # noqa: F811
         C.set_launch(1, 1, v, 0)
         assert torch.equal(C.initial_state(), ref)
         assert float((C.step(ref, n=1) - y).abs().max()) <= 1e-12 * float(y.abs().max())
+
+
+@pytest.mark.parametrize("nz,red", [(2, True), (4, False), (32, False)])
+def test_chunks_where_planes_are_few(B, nz, red):  # noqa: F811
+    """72 tiles of 16 lane groups on 256 compute units: three chunks in one
+    round of workgroups, not fifteen in five rounds, whose set-up each round
+    repeats."""
+    over = dict(vlo=(-4.0, -4.0, -1.0), vhi=(4.0, 4.0, 1.0), reduced=True) if red else {}
+    C = B.Context(prob("cavity", nx=48, ny=48, nv=(32, 32, nz), **over), "fp64", tune="off")
+    assert C.kernel() == "k_tile" and C.launch()["vsplit"] == 3
