@@ -621,18 +621,6 @@ __global__ void k_part_totals(Args A, const double *__restrict__ partial, double
     tot[t] = v;
 }
 
-// The inverse for the current chunk count: slot 0 holds the total, the
-// others zero (so every consumer's slot sum is the total again, exactly).
-__global__ void k_part_restore(Args A, const double *__restrict__ tot, double *__restrict__ partial)
-{
-    const long long t = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= (long long)A.ncells * A.nparts * NQ) return;
-    const long long slot = t / NQ;
-    const int q = (int)(t - slot * NQ);
-    const long long c = slot / A.nparts;
-    partial[t] = slot - c * A.nparts == 0 ? tot[c * NQ + q] : 0.0;
-}
-
 // Per (instance, wall): D = sum_em (v.n) Phi_W and D' = dD/dT_w over the
 // emitted velocities, Phi_W the unit-density wall Maxwellian of the wall's
 // first table entry.  One workgroup per (instance, wall); 0 for non-cavities.

@@ -874,13 +874,15 @@ static Args pointwise_args(const bgk_ctx *c)
     return a;
 }
 
+// Partial sums per cell that the moment pass leaves: its chunks, at most those
+// of the streaming pass (the buffer holds no more).
+static int moment_parts(const bgk_ctx *c) { return std::min(pointwise_args(c).vsplit, num_parts(c)); }
+
 template <typename real>
 static int launch_moments(bgk_ctx *c, const void *f, hipStream_t s)
 {
-    // (the sums fill the nparts slots per cell that the table preparation adds
-    // up: tiles may leave fewer than the chunks of a pointwise pass)
     Args a = pointwise_args(c);
-    a.vsplit = std::min(a.vsplit, a.nparts);
+    a.vsplit = moment_parts(c);
     const int nb = c->ncells * a.vsplit;
     if (pointwise_vec(c) == 4)
         hipLaunchKernelGGL((k_moments<real, 4>), dim3(nb), dim3(pointwise_block(c)), 0, s, a, (const real *)f, c->partial);
@@ -892,14 +894,20 @@ static int launch_moments(bgk_ctx *c, const void *f, hipStream_t s)
     return BGK_OK;
 }
 
+// Moment sums of every cell as their consumers read them: p holds n partial
+// sums per cell (a step record's totals are such sums with n = 1).
+struct Sums { const double *p; int n; };
+static Sums stream_sums(const bgk_ctx *c) { return {c->partial, num_parts(c)}; }
+static Sums moment_sums(const bgk_ctx *c) { return {c->partial, moment_parts(c)}; }
+
 template <typename real>
-static int launch_prep(bgk_ctx *c, int mode, int nparts, int parity, hipStream_t s)
+static int launch_prep(bgk_ctx *c, int mode, Sums m, int parity, hipStream_t s)
 {
     // ghost sources: none after the last pass, and far-field entries, which never
     // change, are written (to both parities) by the opening preparation alone
     const int ne = c->ncells + (mode == MODE_FINAL || (mode == MODE_MID && !c->walls) ? 0 : c->npseudo);
     Args a = make_args(c);
-    a.nparts = nparts;
+    a.nparts = m.n;
     real *copy = mode == MODE_FIRST ? params_buf<real>(c, 1 - parity) : nullptr;
     // lanes per entry: the smallest of 16, 32, 64 that holds the largest velocity axis
     const int nvmax = std::max(c->geo.nvx, std::max(c->geo.nvy, c->geo.nvz));
@@ -907,7 +915,7 @@ static int launch_prep(bgk_ctx *c, int mode, int nparts, int parity, hipStream_t
     const int per_block = 4 * (64 / w);
     real *pb = params_buf<real>(c, parity);
     auto go = [&](auto kern, int blocks) {
-        hipLaunchKernelGGL(kern, dim3(blocks), dim3(256), 0, s, a, c->partial, pb, mode, ne, copy);
+        hipLaunchKernelGGL(kern, dim3(blocks), dim3(256), 0, s, a, m.p, pb, mode, ne, copy);
     };
     const int cb = (c->ncells + per_block - 1) / per_block, gb = (ne - c->ncells + per_block - 1) / per_block;
     // One launch while the cells are few rounds of workgroups: the ghosts' chain
@@ -1166,7 +1174,7 @@ static int one_pass(bgk_ctx *c, int k, int n, const void *src, void *dst, hipStr
 {
     c->pass_parity = (k - 1) % 2;
     TRY(launch_stream<real>(c, src, dst, s));
-    return launch_prep<real>(c, k < n ? MODE_MID : MODE_FINAL, num_parts(c), k % 2, s);
+    return launch_prep<real>(c, k < n ? MODE_MID : MODE_FINAL, stream_sums(c), k % 2, s);
 }
 
 // Every launch of n >= 1 steps after the rounding counter is set: the
@@ -1176,7 +1184,7 @@ template <typename real>
 static int step_launches(bgk_ctx *c, const void *f_in, void *f_out, int n, hipStream_t s)
 {
     TRY(launch_moments<real>(c, f_in, s));
-    TRY(launch_prep<real>(c, MODE_FIRST, num_parts(c), 0, s));
+    TRY(launch_prep<real>(c, MODE_FIRST, moment_sums(c), 0, s));
     auto X = [&](int k) -> void * { return k == 0 ? const_cast<void *>(f_in) : ((n - k) % 2 == 0 ? f_out : c->work); };
     for (int k = 1; k <= n; ++k) TRY(one_pass<real>(c, k, n, X(k - 1), X(k), s));
     return launch_final<real>(c, f_out, f_out, n % 2, s);
@@ -1307,9 +1315,11 @@ static int relax_coef(bgk_ctx *c, const void *x, const void *mu, const double *i
 }
 
 template <typename real>
-static int relax_info(bgk_ctx *c, double *info, int which, hipStream_t s)
+static int relax_info(bgk_ctx *c, Sums m, double *info, int which, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_relax_info, dim3((c->ncells + 255) / 256), dim3(256), 0, s, make_args(c), c->partial, info,
+    Args a = make_args(c);
+    a.nparts = m.n;
+    hipLaunchKernelGGL(k_relax_info, dim3((c->ncells + 255) / 256), dim3(256), 0, s, a, m.p, info,
                        which);
     HIP_TRY(c, hipGetLastError());
     return BGK_OK;
@@ -1443,13 +1453,13 @@ static int do_adjoint(bgk_ctx *c, const void *f, const void *lam_next, void *lam
     TRY(fill(c, c->gk, c->ncells, 0.0, s));
     TRY(fill(c, c->gt, c->ncells, 0.0, s));
     TRY(launch_moments<real>(c, f, s));
-    TRY(relax_info<real>(c, c->info_f, 0, s));
-    TRY(launch_prep<real>(c, MODE_FIRST, num_parts(c), 0, s));
+    TRY(relax_info<real>(c, moment_sums(c), c->info_f, 0, s));
+    TRY(launch_prep<real>(c, MODE_FIRST, moment_sums(c), 0, s));
     c->pass_parity = 0;
     unsigned char *br = (unsigned char *)c->adj_rec;
     if (c->dim == 1) TRY((launch_stream_rec<real, 1>(c, f, c->adj_h, br, s)));
     else TRY((launch_stream_rec<real, 2>(c, f, c->adj_h, br, s)));
-    TRY(relax_info<real>(c, c->info_h, 1, s));
+    TRY(relax_info<real>(c, stream_sums(c), c->info_h, 1, s));
     return adjoint_tail<real>(c, f, c->adj_h, br, lam_next, lam_n, grad, s);
 }
 
@@ -1472,22 +1482,18 @@ static RecordLayout record_layout(const bgk_ctx *c)
     return r;
 }
 
-static int part_totals(bgk_ctx *c, double *tot, hipStream_t s)
+static int part_totals(bgk_ctx *c, Sums m, double *tot, hipStream_t s)
 {
     const long long n = (long long)c->ncells * NQ;
-    hipLaunchKernelGGL(k_part_totals, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, make_args(c), c->partial, tot);
+    Args a = make_args(c);
+    a.nparts = m.n;
+    hipLaunchKernelGGL(k_part_totals, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, a, m.p, tot);
     HIP_TRY(c, hipGetLastError());
     return BGK_OK;
 }
 
-static int part_restore(bgk_ctx *c, const double *tot, hipStream_t s)
-{
-    const long long n = (long long)c->ncells * num_parts(c) * NQ;
-    hipLaunchKernelGGL(k_part_restore, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, make_args(c), tot,
-                       c->partial);
-    HIP_TRY(c, hipGetLastError());
-    return BGK_OK;
-}
+// The totals in a record, as sums.
+static Sums record_sums(const char *rec, size_t tot) { return {(const double *)(rec + tot), 1}; }
 
 // One step that keeps its record: the launch sequence of a one-step
 // bgk_step with the streaming pass in its recording form writing h into the
@@ -1500,14 +1506,14 @@ static int do_step_record(bgk_ctx *c, const void *f_in, void *f_out, char *rec, 
     HIP_TRY(c, hipGetLastError());
     c->seed += 1u;
     TRY(launch_moments<real>(c, f_in, s));
-    TRY(launch_prep<real>(c, MODE_FIRST, num_parts(c), 0, s));
-    TRY(part_totals(c, (double *)(rec + L.tot_f), s));
+    TRY(launch_prep<real>(c, MODE_FIRST, moment_sums(c), 0, s));
+    TRY(part_totals(c, moment_sums(c), (double *)(rec + L.tot_f), s));
     c->pass_parity = 0;
     unsigned char *br = (unsigned char *)(rec + L.br);
     if (c->dim == 1) TRY((launch_stream_rec<real, 1>(c, f_in, rec + L.h, br, s)));
     else TRY((launch_stream_rec<real, 2>(c, f_in, rec + L.h, br, s)));
-    TRY(part_totals(c, (double *)(rec + L.tot_h), s));
-    TRY(launch_prep<real>(c, MODE_FINAL, num_parts(c), 1, s));
+    TRY(part_totals(c, stream_sums(c), (double *)(rec + L.tot_h), s));
+    TRY(launch_prep<real>(c, MODE_FINAL, stream_sums(c), 1, s));
     return launch_final<real>(c, rec + L.h, f_out, 1, s);
 }
 
@@ -1520,11 +1526,9 @@ static int do_adjoint_record(bgk_ctx *c, const void *f, const char *rec, const v
     TRY(ensure_adjoint(c));
     TRY(fill(c, c->gk, c->ncells, 0.0, s));
     TRY(fill(c, c->gt, c->ncells, 0.0, s));
-    TRY(part_restore(c, (const double *)(rec + L.tot_f), s));
-    TRY(relax_info<real>(c, c->info_f, 0, s));
-    TRY(launch_prep<real>(c, MODE_FIRST, num_parts(c), 0, s));
-    TRY(part_restore(c, (const double *)(rec + L.tot_h), s));
-    TRY(relax_info<real>(c, c->info_h, 1, s));
+    TRY(relax_info<real>(c, record_sums(rec, L.tot_f), c->info_f, 0, s));
+    TRY(launch_prep<real>(c, MODE_FIRST, record_sums(rec, L.tot_f), 0, s));
+    TRY(relax_info<real>(c, record_sums(rec, L.tot_h), c->info_h, 1, s));
     return adjoint_tail<real>(c, f, rec + L.h, (const unsigned char *)(rec + L.br), lam_next, lam_n, grad, s);
 }
 
@@ -1548,20 +1552,17 @@ static int do_adjoint_sweep(bgk_ctx *c, int n, const void *const *f, const void 
     auto lam_in = [&](int i) -> const void * { return i + 1 == n ? lam_N : (const void *)lam_out(i + 1); };
     for (int i = n - 1; i >= 0; --i) {
         // step i's opening relaxation data and tables
-        TRY(part_restore(c, (const double *)(R(i) + L.tot_f), s));
-        TRY(relax_info<real>(c, c->info_f, 0, s));
-        TRY(launch_prep<real>(c, MODE_FIRST, num_parts(c), 0, s));
+        TRY(relax_info<real>(c, record_sums(R(i), L.tot_f), c->info_f, 0, s));
+        TRY(launch_prep<real>(c, MODE_FIRST, record_sums(R(i), L.tot_f), 0, s));
         if (i == n - 1 || !fuse) {
             // R_b^T coefficients of step i from its own sums at h
-            TRY(part_restore(c, (const double *)(R(i) + L.tot_h), s));
-            TRY(relax_info<real>(c, c->info_h, 1, s));
+            TRY(relax_info<real>(c, record_sums(R(i), L.tot_h), c->info_h, 1, s));
             TRY(relax_coef<real>(c, R(i) + L.h, lam_in(i), c->info_h, s));
         }
         TRY(adj_gather_wall<real>(c, (const unsigned char *)(R(i) + L.br), lam_in(i), s));
         if (fuse && i > 0) {
             // lambda^i, and with it step i-1's sums at h and its R_b^T coefficients
-            TRY(part_restore(c, (const double *)(R(i - 1) + L.tot_h), s));
-            TRY(relax_info<real>(c, c->info_h, 1, s));
+            TRY(relax_info<real>(c, record_sums(R(i - 1), L.tot_h), c->info_h, 1, s));
             hipLaunchKernelGGL((k_adj_close<real, true>), dim3(c->ncells), dim3(fit_block(c->geo.npl)), 0, s,
                                make_args(c), (const real *)f[i], (const real *)c->adj_hb, c->info_f, c->gk,
                                (real *)lam_out(i), (const real *)(R(i - 1) + L.h), (const double *)c->info_h,
@@ -1844,7 +1845,7 @@ template <typename real>
 static int autotune(bgk_ctx *c, const void *f, void *tmp, hipStream_t s)
 {
     TRY(launch_moments<real>(c, f, s));
-    TRY(launch_prep<real>(c, MODE_FIRST, num_parts(c), 0, s));
+    TRY(launch_prep<real>(c, MODE_FIRST, moment_sums(c), 0, s));
     struct Cand { double us; int vec, unroll, vsplit, persist; };
     const Cand start{0.0, c->vec, c->unroll, use_tile(c) ? c->tsplit : c->vsplit, c->persist};
     std::vector<Cand> cands;
@@ -1979,7 +1980,9 @@ extern "C" int bgk_moments(bgk_ctx *ctx, const void *f, double *mom, void *strea
     if (!f || !mom) return fail(ctx, BGK_E_INVALID, "bgk_moments: NULL buffer");
     hipStream_t s = (hipStream_t)stream;
     TRY(ctx->precision == BGK_FP64 ? launch_moments<double>(ctx, f, s) : launch_moments<float>(ctx, f, s));
-    hipLaunchKernelGGL(k_macro, dim3((ctx->ncells + 255) / 256), dim3(256), 0, s, make_args(ctx), ctx->partial, mom);
+    Args a = make_args(ctx);
+    a.nparts = moment_parts(ctx);
+    hipLaunchKernelGGL(k_macro, dim3((ctx->ncells + 255) / 256), dim3(256), 0, s, a, ctx->partial, mom);
     HIP_TRY(ctx, hipGetLastError());
     return BGK_OK;
 }

@@ -428,7 +428,7 @@ __device__ __forceinline__ double wave_sum(double x)
 
 // ---------------------------------------------------------------- moments
 // Partial moment sums of f over one jz chunk of one cell:
-// partial[(cell * nparts + split) * NQ + q] (without the dV factor).  Each
+// partial[(cell * vsplit + split) * NQ + q] (without the dV factor).  Each
 // lane reads VEC consecutive jx at one jy (16-byte loads where the grid
 // allows) down its jz chunk.  Bound by the read of f (4.2 TB/s on large
 // grids, 5.0 with whole pages per cell); the sums meet by lane moves, not
@@ -475,10 +475,8 @@ __global__ void __launch_bounds__(256) k_moments(Args A, const real *__restrict_
             fold_column(acc, vnode(g, 0, jx0 + e), vnode(g, 1, jy), A0[e], e == 0 ? Az : 0.0, e == 0 ? Azz : 0.0,
                         e == 0 ? Azm : 0.0, e == 0 ? Azp : 0.0);
     }
-    // slot (cell, split) of the A.nparts per cell the consumers add up; a
-    // launch with fewer chunks than slots zeroes the remaining ones.  The five
-    // moments, and for cells at a wall the half-range fluxes (nothing reads
-    // those of other cells)
+    // the five moments, and for cells at a wall the half-range fluxes (nothing
+    // reads those of other cells)
     const int c = gc - I.cell0, ix = c % I.nx, iy = c / I.nx % I.ny, iz = c / I.nx / I.ny;
     const bool wall = (I.kind == KIND_CAVITY || I.kind == KIND_CAV3) &&
                       (ix == 0 || ix == I.nx - 1 || iy == 0 || iy == I.ny - 1 ||
@@ -498,11 +496,8 @@ __global__ void __launch_bounds__(256) k_moments(Args A, const real *__restrict_
     if (threadIdx.x < NQ) {
         double t = 0.0;
         for (int k = 0; k < nw; ++k) t += red[k][threadIdx.x];
-        partial[((long long)gc * A.nparts + split) * NQ + threadIdx.x] = t;
+        partial[(long long)L * NQ + threadIdx.x] = t;
     }
-    if (split == 0)
-        for (int t = threadIdx.x; t < (A.nparts - A.vsplit) * NQ; t += blockDim.x)
-            partial[((long long)gc * A.nparts + A.vsplit) * NQ + t] = 0.0;
 }
 
 // Per-cell macroscopic moments (n, Vx, Vy, Vz, T) from the partial sums.

@@ -94,3 +94,18 @@ def test_chunks_where_planes_are_few(B, nz, red):  # noqa: F811
     over = dict(vlo=(-4.0, -4.0, -1.0), vhi=(4.0, 4.0, 1.0), reduced=True) if red else {}
     C = B.Context(prob("cavity", nx=48, ny=48, nv=(32, 32, nz), **over), "fp64", tune="off")
     assert C.kernel() == "k_tile" and C.launch()["vsplit"] == 3
+
+
+def test_reverse_step_from_a_record_at_any_chunk_count(B):  # noqa: F811
+    """A record's totals serve the reverse step as they are, whatever number
+    of partial sums the tiles leave when it runs."""
+    C = B.Context(prob("cavity", nx=26, ny=25, nv=(14, 11, 5)), "fp64", tune="off")
+    x = C.initial_state()
+    x = x * (1 + 0.2 * torch.tensor(inputs.uniform((C.f_elems,), seed=8, lo=-1, hi=1), device="cuda"))
+    lam = torch.tensor(inputs.uniform((C.f_elems,), seed=9, lo=-1, hi=1), device="cuda")
+    _, rec = C.step_record(x)
+    ref, gref = C.step_adjoint_record(x, rec, lam)
+    for v in (1, 2, 3):
+        C.set_launch(1, 1, v, 0)
+        got, g = C.step_adjoint_record(x, rec, lam)
+        assert torch.equal(got, ref) and torch.equal(g, gref)
