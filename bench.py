@@ -72,7 +72,9 @@ def kernel_source_hash() -> str:
 
 def read_traffic(workload: str, kname: str = "k_stream"):
     """HBM bytes per streaming launch from a committed counter summary
-    (profiles/<kernel>_<workload>_counters.txt), if taken from these kernels."""
+    (profiles/<form>_<workload>_counters.txt, form k_stream for the per-cell
+    and tile kernels and k_shift for the translation form's; its first line
+    names the kernel), if taken from these kernels."""
     path = os.path.join(PROFILES, f"{kname}_{workload}_counters.txt")
     if not os.path.exists(path):
         return None
@@ -172,7 +174,8 @@ def run_workload(binding, torch, problems, precision, steps, warmup, kernel_timi
     replay, as one replay of the graph that an untimed call of the same step
     count captured after the warm-up (wall clock only: HIP reports no
     elapsed time for events that graph nodes record).  Returns (seconds for
-    `steps`, kernel ms per launch or NaN, points, launch shape)."""
+    `steps`, kernel ms per pass or NaN, points, launch shape, the streaming
+    kernel's name)."""
     ctx = binding.Context(problems, precision)
     points = ctx.f_elems
     x = ctx.initial_state()
@@ -180,7 +183,7 @@ def run_workload(binding, torch, problems, precision, steps, warmup, kernel_timi
     torch.cuda.synchronize()
     if tune:
         ctx.autotune(x)
-    shape = ctx.launch()
+    shape, kernel = ctx.launch(), ctx.kernel()
     stream = torch.cuda.Stream() if graph else torch.cuda.current_stream()  # graphs need a capturable stream
     with torch.cuda.stream(stream):
         ctx.set_graph(graph)
@@ -208,7 +211,7 @@ def run_workload(binding, torch, problems, precision, steps, warmup, kernel_timi
     torch.cuda.empty_cache()
     if rc != 0:
         raise RuntimeError(f"state check failed after the timed run (status {rc})")
-    return t1 - t0, ms / max(launches, 1), points, shape
+    return t1 - t0, ms / max(launches, 1), points, shape, kernel
 
 
 def run_adjoint(binding, torch, cfg, precision, every=None, mode="auto"):
@@ -430,13 +433,13 @@ def main():
         return
     probs, prec = workload(inputs, args.workload)
     graph = args.graph
-    secs, kms, points, shape = run_workload(binding, torch, probs, prec, args.steps, args.warmup,
-                                            not args.no_kernel_timing, not args.no_tune, graph)
+    secs, kms, points, shape, kname = run_workload(binding, torch, probs, prec, args.steps, args.warmup,
+                                                   not args.no_kernel_timing, not args.no_tune, graph)
     value = points * args.steps / secs
     bpu = bytes_per_update(prec)
     achieved = bpu * points / (kms * 1e-3) / 1e9
-    kname = "k_shift" if probs[0].get("limiter") == "shift" else "k_stream"  # the streaming kernel of this workload
-    traffic = read_traffic(args.workload, kname)
+    # (counter summaries are named by the form of the pass, whichever of its kernels ran)
+    traffic = read_traffic(args.workload, "k_shift" if kname.startswith("k_shift") else "k_stream")
     cells = sum(inputs.ncells(q) for q in probs)
     out = {
         "metric": "phase-space point updates/s",
@@ -499,11 +502,11 @@ def main():
                 continue
             wname = BATCH if name.startswith(BATCH) else name
             wprobs, _ = workload(inputs, wname)
-            s, k, pts, shp = run_workload(binding, torch, wprobs, p, steps, warm, True, True, graph_x)
+            s, k, pts, shp, kern = run_workload(binding, torch, wprobs, p, steps, warm, True, True, graph_x)
             cells_x = sum(inputs.ncells(q) for q in wprobs)
             e = {"updates_per_s": pts * steps / s, "ns_per_update": s / (pts * steps) * 1e9, "steps": steps,
                  "points": pts, "cell_steps_per_s": cells_x * steps / s, "launch": shp, "precision": p,
-                 "graph": graph_x, "kernel": "k_shift" if wprobs[0].get("limiter") == "shift" else "k_stream"}
+                 "graph": graph_x, "kernel": kern}
             if k == k:  # timed kernels (not NaN)
                 a = bytes_per_update(p) * pts / (k * 1e-3) / 1e9
                 e.update({"kernel_ms": k, "achieved_GBs": a, "frac": a / PEAK_HBM_GBS})
