@@ -209,8 +209,10 @@ __global__ void __attribute__((amdgpu_flat_work_group_size(64 * TileShape<real, 
     // own branches spills: 128^2 x 24^3 FP32 552 us a step, 504 with this.)
     const bool walls = I.kind == KIND_CAVITY;
     const int reach = walls ? 2 : 0;
-    const bool edge = x0 + S::TX + reach > I.nx || (walls && x0 == 0) ||
-                      (DIM == 2 && (y0 + S::TY + reach > I.ny || (walls && y0 == 0)));
+    // (forced into a scalar register: three spilled registers fewer)
+    const bool edge = __builtin_amdgcn_readfirstlane(
+        (int)(x0 + S::TX + reach > I.nx || (walls && x0 == 0) ||
+              (DIM == 2 && (y0 + S::TY + reach > I.ny || (walls && y0 == 0))))) != 0;
     const bool wall = cx0 == 0 || cx0 + 4 >= I.nx || cy0 == 0 || cy0 + 1 >= I.ny;  // the wave has wall cells
     const bool xh = DIM == 2 || wave < 2;  // the wave has x-halo rows
     real c0[RPW];                           // the rows' c0 (wave-uniform)
