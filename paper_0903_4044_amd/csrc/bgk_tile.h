@@ -191,12 +191,18 @@ __global__ void __attribute__((amdgpu_flat_work_group_size(64 * TileShape<real, 
     // ---- this wave's rows
     uint32_t roff[RPW];     // byte offset of the row's h in the instance
     int gm = 0;             // rows with a ghost part
+    // double: the ghost's column behind the row's own, in bytes (in float these
+    // scalars cost vector registers that are not there: 128^2 x 24^3 496 us a
+    // step without them, 624 with; 48^2 x 24^3 FP64 177 without, 167 with)
+    int dcol[sizeof(real) == 8 ? RPW : 1];
     bool out[4];            // cells inside the instance
     const TileRow *const rows = s_row + wave * RPW;
 #pragma unroll
     for (int r = 0; r < RPW; ++r) {
         roff[r] = __builtin_amdgcn_readfirstlane(rows[r].off) * (uint32_t)sizeof(real);
         if (DIM == 2 && __builtin_amdgcn_readfirstlane(rows[r].code)) gm |= 1 << r;
+        if constexpr (sizeof(real) == 8)
+            dcol[r] = (__builtin_amdgcn_readfirstlane(rows[r].gcol) - (wave * RPW + r)) * 2 * (int)sizeof(real);
     }
     const int cx0 = x0 + (DIM == 1 ? 4 * wave : 4 * (wave & 1)), cy0 = y0 + (DIM == 1 ? 0 : wave >> 1);
 #pragma unroll
@@ -320,9 +326,11 @@ __global__ void __attribute__((amdgpu_flat_work_group_size(64 * TileShape<real, 
             for (int q = 0; q < HALF && b0 + q < RPW; ++q) {
                 const int r = b0 + q;
                 const unsigned char *zp = Z + r * 2 * sizeof(real);
-                if (EDGE && (gm >> r & 1)) {
-                    const int dcol = __builtin_amdgcn_readfirstlane(rows[r].gcol) - (wave * RPW + r);
-                    if (em >> r & 1) zp += dcol * 2 * (int)sizeof(real);
+                if constexpr (sizeof(real) == 8) {
+                    if (EDGE) zp += dcol[r] & ((em << (31 - r)) >> 31);
+                } else if (EDGE && (gm >> r & 1)) {
+                    const int d = __builtin_amdgcn_readfirstlane(rows[r].gcol) - (wave * RPW + r);
+                    if (em >> r & 1) zp += d * 2 * (int)sizeof(real);
                 }
                 ab[q] = *reinterpret_cast<const R2 *>(zp);
             }
