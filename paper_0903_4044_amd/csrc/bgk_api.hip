@@ -470,13 +470,16 @@ static void plan_tile(bgk_ctx *c)
     }
     // Where the per-cell kernel stays: too few (tile, p-group) units to fill the
     // device (a unit of 24 planes takes ~40 us whatever the grid), or tiles
-    // largely outside the domain.  Steps measured as per-cell / tile, us:
-    // FP32 2D 33x29 x 24^3 (180 units, 256 slots) 79 / 72, 24x24 (81) 63 / 75,
-    // 17x150 (padded 1.43 times) 159 / 173; FP64 2D 33x29 x 16^3 (160 of 256)
-    // 75 / 53, 16x16 (32) 52 / 52; FP32 1D 256 x 48^3 (576 of 1024) 93 / 87,
-    // 2000 x 16^3 (500) 31 / 33; FP64 1D 2000 x 32^3 (2000 of 512) 278 / 234,
-    // 700 (704) 107 / 107, 256 (256) 36 / 45; FP32 3D x 16^3 24^3 cells (864 of
-    // 256, two launches) 409 / 364, 20^3 (500) 245 / 267, 40 x 24 x 12 (720) 349 / 358.
+    // largely outside the domain.  Steps measured as per-cell / tile, us (units
+    // of the slots):
+    // FP32 2D 33x29 x 24^3 (180 of 256) 79 / 64, 24x24 (81) 62 / 66, 17x150
+    // (padded 1.43 times) 158 / 163; FP64 2D 33x29 x 16^3 (160 of 256) 76 / 50,
+    // 16x16 (32) 52 / 47; FP32 1D 256 x 48^3 (576 of 1024) 93 / 72, 2000 x 16^3
+    // (500) 31 / 26; FP64 1D 2000 x 32^3 (2000 of 512) 282 / 221, 700 (704)
+    // 109 / 107, 256 (256) 37 / 37; FP32 3D x 16^3 24^3 cells (864 of 256, two
+    // launches) 414 / 363, 20^3 (500) 248 / 266, 40 x 24 x 12 (720) 351 / 357.
+    // (The lines of 1D and of FP64 2D were drawn before far-field rows lost their
+    // selection and ghost columns their loads; tiles gain a little below them too.)
     const bool d = c->precision == BGK_FP64;
     const double fill = c->dim == 3 ? 3.3 : c->dim == 2 ? (d ? 0.25 : 0.7) : (d ? 2.0 : 0.55), pad = d ? 1.7 : 1.35;
     if ((double)tiles * P.npg < fill * P.slots || (double)tiles * P.tx * P.ty * P.tz > pad * c->ncells) return;

@@ -4,14 +4,16 @@
 // velocity itself, here a workgroup relaxes each cell of a tile and of its
 // halo once and the stencils read the relaxed values from LDS.
 //
-// Bound by the issue of vector instructions: k_stream spends ~76 per element
-// on 2D grids, most of them on the seven relaxations and their table loads;
-// here a plane of 64 (jx, jy) of 4 cells takes ~180 (45 per element) with the
-// loads of the next plane in flight.  128^2 x 24^3 FP32: 510 us a pass for the
-// 1.81 GB of f (3.5 TB/s), 790 in k_stream; 160^2 x 20^3 595 (2.8 TB/s), 1096;
-// 48 cavities of up to 160^2 8.4 ms, 13.2; 48^2 x 24^3 FP64 159 us (3.2 TB/s),
-// 272; 1024 x 48^3 FP32 217 us (4.2 TB/s), 272; recording on 64^2 x 24^3
-// FP32 201, 231.
+// In one and two dimensions bound by the memory traffic: 1024 x 48^3 FP32
+// moves 0.93 GB (1.03 times f's read and write) in 184 to 198 us, 128^2 x 24^3
+// 2.26 GB (1.25 times: halo rows read again, spilled registers) in 462 to 480,
+// 64 cavities 62 GB (1.32 times) in 12.1 ms, 4.7 to 5.2 TB/s where a large copy
+// reaches 4.9.  The issue of vector instructions is not far behind: 49 per
+// element in 2D (76 in k_stream, most of them its seven relaxations and their
+// table loads), with the loads of the next plane in flight.  In k_stream these
+// passes took 272 us, 790 us and 19.6 ms.  160^2 x 20^3 FP32 558 to 585 us,
+// 1096 there; 48^2 x 24^3 FP64 154 us, 272; recording on 64^2 x 24^3 FP32 205,
+// 231.
 #pragma once
 
 #include "bgk_device.h"
@@ -22,11 +24,11 @@ namespace bgk {
 // plane holds the tile and two halo cells on every side, position
 // (y + 2 HY) * PITCH + x + 2; each position holds one value per lane.
 // Waves per workgroup: in 2D the halo of 8 x 8 cells doubles the relaxed
-// values, that of 8 x 4 cells makes it 2.5 times (float: 519 against 577 us a
+// values, that of 8 x 4 cells makes it 2.5 times (float: 499 against 554 us a
 // step on 128^2 x 24^3); in FP64 the two LDS planes of 8 x 8 cells and the
 // registers of 16 waves do not fit.  In 1D the halo is small and the short
-// workgroups balance better (1024 x 48^3: 224 us a step with 4 waves, 240
-// with 8, 255 with 16).
+// workgroups balance better (1024 x 48^3: 203 us a step with 4 waves, 212
+// with 8, 210 with 16).
 template <typename real, int DIM>
 struct TileShape {
     static constexpr int NW = DIM == 1 ? 4 : sizeof(real) == 4 ? 16 : 8;
@@ -467,9 +469,9 @@ __global__ void __attribute__((amdgpu_flat_work_group_size(64 * TileShape<real, 
 // Tiles at a boundary (EDGE) and inner ones run as kernels of their own: the
 // ghosts' selection compiled into one kernel with the inner path spills both.
 // Bound by the issue of vector instructions (53 to 60 per output, 55% of the
-// cycles at two waves a SIMD) and the barriers.  48^3 cells x 16^3 FP32: 1.08 ms
-// (1000 inner tiles) + 1.08 (728 at the walls) a pass, 3.55 in k_stream;
-// 48^3 x 12^3 a step 1.30 ms, 3.97; 36 x 28 x 32 x 20^3 1.72, 2.29.
+// cycles at two waves a SIMD) and the barriers.  48^3 cells x 16^3 FP32: 1.03 ms
+// (1000 inner tiles) + 1.04 (728 at the walls) a pass, 3.55 in k_stream;
+// 48^3 x 12^3 a step 1.30 ms, 3.97; 36 x 28 x 32 x 20^3 1.71, 2.29.
 struct Tile3 {
     static constexpr int T = 4, NW = 8, RPW = 32, NROW = NW * RPW;  // cells per side, waves, rows
     // LDS positions: the lines' 8 cells each, then the y and the z halo lines
