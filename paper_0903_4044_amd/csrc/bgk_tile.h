@@ -12,7 +12,7 @@
 // element in 2D (76 in k_stream, most of them its seven relaxations and their
 // table loads), with the loads of the next plane in flight.  In k_stream these
 // passes took 272 us, 790 us and 19.6 ms.  160^2 x 20^3 FP32 558 to 585 us,
-// 1096 there; 48^2 x 24^3 FP64 154 us, 272; recording on 64^2 x 24^3 FP32 205,
+// 1096 there; 48^2 x 24^3 FP64 154 us, 272; recording on 64^2 x 24^3 FP32 199,
 // 231.
 #pragma once
 
